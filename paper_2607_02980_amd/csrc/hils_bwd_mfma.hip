@@ -812,8 +812,7 @@ struct BwRun {
         HILS_LAUNCH("k_bwd_u", (k_bwd_u<D>), dim3((unsigned)((rows + upb - 1) / upb)), dim3(kBlock), 0, s, a, u);
         const InvArgs ia{a.idx, a.B, a.Hkv, a.N, a.K, a.W, a.L, 0, a.N};
         launch_inverse_index(ia, ly.inv, a.ws, s, false);
-        HILS_LAUNCH("k_inv_sort", k_inv_sort, dim3(nC, a.B * a.Hkv), dim3(kBlock), 0, s, offsets,
-                    reinterpret_cast<const int*>(ws + ly.inv.list), sorted, a.N, a.K, nC, a.W);
+        launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
         if (a.q_route)
             HILS_LAUNCH("k_bwd_keys", (k_bwd_keys<D, G, true>), dim3(nC, a.Hkv, a.B), dim3(kKeyThreads), 0, s, a, offsets,
                         (const int*)sorted, (const float*)u, dqp, dsh);
@@ -832,6 +831,14 @@ struct BwRun {
 };
 
 }  // namespace
+
+void launch_inv_sort(const InvArgs& a, const InvLayout& w, void* ws, int* sorted, hipStream_t s) {
+    const char* base = static_cast<const char*>(ws);
+    const int nC = a.L / kChunk;
+    HILS_LAUNCH("k_inv_sort", k_inv_sort, dim3(nC, a.B * a.Hkv), dim3(kBlock), 0, s,
+                reinterpret_cast<const int*>(base + w.offsets), reinterpret_cast<const int*>(base + w.list), sorted,
+                a.N, a.K, nC, a.W);
+}
 
 size_t bwd_mfma_workspace_bytes(int B, int Hq, int Hkv, int N, int L, int d, int K) {
     return bw_layout(B, Hq, Hkv, N, L, d, K).total;

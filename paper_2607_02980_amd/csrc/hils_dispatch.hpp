@@ -27,6 +27,17 @@ hipError_t dispatch(int bf16_storage, int d, int G, A&&... args) {
     return hipErrorInvalidValue;
 }
 
+// Calls F::template run<D, G>(args...) for the runtime (d, G); fp32 storage only.
+template <typename F, typename... A>
+hipError_t dispatch_f32(int d, int G, A&&... args) {
+#define HILS_CASE(DD, GG) \
+    if (d == DD && G == GG) return F::template run<DD, GG>(args...);
+    HILS_CASE(64, 1) HILS_CASE(64, 2) HILS_CASE(64, 4) HILS_CASE(64, 8)
+    HILS_CASE(128, 1) HILS_CASE(128, 2) HILS_CASE(128, 4) HILS_CASE(128, 8)
+#undef HILS_CASE
+    return hipErrorInvalidValue;
+}
+
 template <typename T>
 __device__ __forceinline__ const T* as(const void* p) {
     return reinterpret_cast<const T*>(p);

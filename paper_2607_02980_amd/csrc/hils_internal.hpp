@@ -121,11 +121,9 @@ InvLayout inv_layout(int B, int Hkv, int N, int L, int K, size_t base, int row_e
 // read them).
 void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStream_t s, bool work_list = true);
 
-// Workspace layout of the backward (byte offsets from ws).
-struct BwdWorkspace {
-    size_t counts, offsets, cursor, list, total;
-};
-BwdWorkspace bwd_workspace_layout(int B, int Hkv, int N, int L, int K);
+// Copies every (b, g, chunk) list of the index to `sorted` ([bg][N * K]) in ascending row
+// order, so that sums over a list have one order.
+void launch_inv_sort(const InvArgs& a, const InvLayout& w, void* ws, int* sorted, hipStream_t s);
 
 // Compute units of the current device (a host-side attribute query; nothing cached).
 int device_cus();
@@ -139,6 +137,7 @@ size_t prefill_record_cap(size_t bytes);
 
 hipError_t launch_prefill_fwd(const FwdArgs& a, hipStream_t s);
 hipError_t launch_prefill_rows(const FwdArgs& a, hipStream_t s);  // fp32 storage
+hipError_t launch_attn_f32(const FwdArgs& a, hipStream_t s);      // its attention over idx
 hipError_t launch_decode_fwd(const FwdArgs& a, hipStream_t s);
 // The no-allocation decode's file-scope device array: its size, and its device
 // address on the current device (looked up once per device).
@@ -147,7 +146,9 @@ hipError_t decode_noalloc_scratch(void** ptr);
 hipError_t launch_landmark_fwd(const LmkArgs& a, hipStream_t s);
 hipError_t launch_landmark_bwd(const LmkArgs& a, hipStream_t s);
 size_t landmark_workspace_bytes(int B, int Hl, int nC, int d, bool shared);
-hipError_t launch_bwd(const BwdArgs& a, hipStream_t s);       // fp32 storage
+hipError_t launch_bwd(const BwdArgs& a, hipStream_t s);
+hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t s);   // fp32 storage
+size_t bwd_f32_workspace_bytes(int B, int Hq, int Hkv, int N, int L, int d, int K, int W);
 hipError_t launch_bwd_mfma(const BwdArgs& a, hipStream_t s);  // bf16 storage
 size_t bwd_mfma_workspace_bytes(int B, int Hq, int Hkv, int N, int L, int d, int K);
 
