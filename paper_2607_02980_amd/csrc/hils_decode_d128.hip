@@ -1,0 +1,8 @@
+// The decode kernels of head dim 128 (one source per head dim, compiled side by side).
+#include "hils_decode.hpp"
+
+namespace hils {
+
+hipError_t launch_decode_d128(const FwdArgs& a, hipStream_t s) { return dispatch_decode<128>(a, s); }
+
+}  // namespace hils

@@ -139,6 +139,8 @@ hipError_t launch_prefill_fwd(const FwdArgs& a, hipStream_t s);
 hipError_t launch_prefill_rows(const FwdArgs& a, hipStream_t s);  // fp32 storage
 hipError_t launch_attn_f32(const FwdArgs& a, hipStream_t s);      // its attention over idx
 hipError_t launch_decode_fwd(const FwdArgs& a, hipStream_t s);
+hipError_t launch_decode_d64(const FwdArgs& a, hipStream_t s);
+hipError_t launch_decode_d128(const FwdArgs& a, hipStream_t s);
 // The no-allocation decode's file-scope device array: its size, and its device
 // address on the current device (looked up once per device).
 size_t decode_noalloc_capacity();
