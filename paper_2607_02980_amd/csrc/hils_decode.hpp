@@ -146,7 +146,7 @@ struct PartSmem {
 
 // NQ: new queries of one sequence scored together (one landmark read for all).
 template <int G, int NQ>
-struct ScanSmem {
+struct __align__(16) ScanSmem {
     float score[NQ][G][kSlice];
     float sig[NQ][kSlice];
     int id[kSlice];
@@ -406,7 +406,7 @@ __device__ void run_part_mfma(const FwdArgs& a, const DecLayout& ly, PartSmemM<D
 // round covers all the slices' survivors where it can.  The result, ascending
 // chunk ids, is left in ms.bid[0, ms.nbest).
 template <int NW>
-struct MergeSmem {
+struct __align__(16) MergeSmem {
     int wid[NW][64], tid[NW][64], bid[64];
     float wsc[NW][64], tsc[NW][64], bsc[64];
     int wn[NW], nbest;
@@ -976,7 +976,7 @@ __global__ __launch_bounds__(kBlock) void k_dec_scan(FwdArgs a, DecLayout ly, in
 template <int E>
 __global__ __launch_bounds__(kBlock) void k_dec_hnsel(FwdArgs a, DecLayout ly, int G, int D) {
     __shared__ int s_oid[kBlock / kWave][64], s_tid[kBlock / kWave][64];
-    __shared__ float s_osc[kBlock / kWave][64], s_tsc[kBlock / kWave][64];
+    __shared__ __align__(16) float s_osc[kBlock / kWave][64], s_tsc[kBlock / kWave][64];
     const int w = wave_id(), lane = threadIdx.x % kWave;
     const int g = blockIdx.y, b = blockIdx.z / a.N, n = blockIdx.z % a.N;
     const size_t rg = ((size_t)b * a.Hkv + g) * a.N + n;

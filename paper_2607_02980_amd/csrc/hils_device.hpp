@@ -249,7 +249,9 @@ __device__ inline int wave_topk(const float* sc, const int* id, int n, int K, in
 // register FIRST (if >= 0) is taken first and then registers 0, 1, ... in turn;
 // the compaction position is then the ascending rank and out_* are written
 // directly.
+// tmp_sc is 16-byte aligned.
 constexpr int kTopkUnordered = -2, kTopkNatural = -1;
+constexpr int kRankMax = 40;  // survivors ranked by counting (20 instructions per 4; more: 32 ballot steps)
 
 // m-th largest value of one NB-bit key per lane (0 if fewer than m lanes hold
 // a key >= 1): the bits of the threshold from the top, one ballot each.
@@ -325,6 +327,37 @@ __device__ inline int wave_topk_reg(const float (&sc)[E], const int (&id)[E], co
             if (have) {
                 const uint32_t k = ordered_key(s1);
                 k1 = k ? k : 1u;
+            }
+            if (kOrdered && c <= kRankMax) {
+                // few survivors, ascending by id over the lanes: each counts the ones
+                // ahead of it (larger key, or the same and a smaller id), four per LDS read;
+                // the scalar unit, which the ballot steps below would keep busy (5
+                // instructions each, one unit for the CU's four SIMDs), has nothing to do
+                uint32_t* keys = reinterpret_cast<uint32_t*>(tmp_sc);
+                __builtin_amdgcn_wave_barrier();
+                keys[lane] = k1;  // 0 past the survivors: ahead of none
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                int ahead = 0;
+                for (int j = 0; j < c; j += 4) {
+                    const uint4 k4 = *reinterpret_cast<const uint4*>(keys + j);
+                    ahead += k4.x > k1 - (j < lane ? 1u : 0u);
+                    ahead += k4.y > k1 - (j + 1 < lane ? 1u : 0u);
+                    ahead += k4.z > k1 - (j + 2 < lane ? 1u : 0u);
+                    ahead += k4.w > k1 - (j + 3 < lane ? 1u : 0u);
+                }
+                const bool pr = have && ahead < m;
+                const uint64_t bal = __ballot(pr);
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int pos = popc64(bal & ((1ull << lane) - 1ull));
+                if (pr) {
+                    out_id[pos] = i1;
+                    out_sc[pos] = s1;
+                }
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                return m;
             }
             const uint32_t T1 = wave_kth_key(k1, m);  // >= T0 >= 1
             const int cnt_gt = (T1 == 0xffffffffu) ? 0 : popc64(__ballot(k1 > T1));
