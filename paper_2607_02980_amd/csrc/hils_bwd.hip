@@ -36,15 +36,35 @@ __global__ void k_fill_i32(int* p, size_t n, int v) {
 // one chunk that fall in one range of rows (the chunk pass walks the buckets in
 // order, so the query rows it gathers stay in L2).
 // List entries are (n << 6) | slot (slot < K <= 64).
-constexpr int kInvRows = 256;
+constexpr int kInvRows = 128;
 constexpr int kInvHist = 8192;  // chunks counted in LDS; larger L falls back to global atomics
 static_assert(kInvBucketRows % kInvRows == 0, "a block of rows lies in one bucket");
 
-// (n: the row relative to a.n0)
-__device__ __forceinline__ bool entry_valid(const InvArgs& a, const int32_t* irow, int slot, int n, int* c) {
-    if (!idx_entry_valid(irow, slot, n_candidates(a.n0 + n, a.W))) return false;
-    *c = irow[slot];
-    return true;
+// The entries of rows n0 .. n0 + rows - 1, kPer per thread and round with their loads in
+// flight together: f(chunk, entry) for the valid ones.
+template <typename F>
+__device__ __forceinline__ void for_entries(const InvArgs& a, int bg, int n0, int rows, F&& f) {
+    constexpr int kPer = 4;
+    const int32_t* idx = a.idx + ((size_t)bg * a.Nrow + a.n0 + n0) * a.K;
+    const int total = rows * a.K;
+    for (int e0 = threadIdx.x; e0 < total; e0 += kPer * kBlock) {
+        int c[kPer], before[kPer];
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            const int e = min(e0 + t * kBlock, total - 1);
+            c[t] = idx[e];
+            before[t] = idx[max(e - 1, 0)];
+        }
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            const int e = e0 + t * kBlock;
+            if (e >= total) break;
+            // (as idx_entry_valid)
+            const int n = n0 + e / a.K, slot = e % a.K;
+            if (c[t] >= 0 && c[t] < n_candidates(a.n0 + n, a.W) && (slot == 0 || c[t] > before[t]))
+                f(c[t], (n << 6) | slot);
+        }
+    }
 }
 
 // grid (ceil(N / kInvRows), B*Hkv); counts [bg][nR][nC] (a block's counters are
@@ -54,63 +74,51 @@ __global__ __launch_bounds__(kBlock) void k_inv_count(InvArgs a, int nR, int bro
     const int bg = blockIdx.y, n0 = blockIdx.x * kInvRows, tid = threadIdx.x;
     const int nC = a.L / kChunk, R = n0 / brows;
     const bool lds = nC <= kInvHist;
-    int* gcnt = counts + (size_t)bg * nC * nR;
+    int* gcnt = counts + (size_t)bg * nC * nR + (size_t)R * nC;
     if (lds)
         for (int c = tid; c < nC; c += kBlock) s_hist[c] = 0;
     __syncthreads();
-    const int rows = min(kInvRows, a.N - n0);
-    for (int e = tid; e < rows * a.K; e += kBlock) {
-        const int n = n0 + e / a.K, slot = e % a.K;
-        const int32_t* irow = a.idx + ((size_t)bg * a.Nrow + a.n0 + n) * a.K;
-        int c;
-        if (!entry_valid(a, irow, slot, n, &c)) continue;
+    for_entries(a, bg, n0, min(kInvRows, a.N - n0), [&](int c, int) {
         if (lds)
             atomicAdd(&s_hist[c], 1);
         else
-            atomicAdd(&gcnt[R * nC + c], 1);
-    }
+            atomicAdd(&gcnt[c], 1);
+    });
     __syncthreads();
     if (lds)
         for (int c = tid; c < nC; c += kBlock)
-            if (s_hist[c]) atomicAdd(&gcnt[R * nC + c], s_hist[c]);
+            if (s_hist[c]) atomicAdd(&gcnt[c], s_hist[c]);
 }
 
-__global__ __launch_bounds__(kBlock) void k_inv_fill(InvArgs a, int nR, int brows, const int* boff, int* cursor,
-                                                     int* list) {
+// cursor [bg][nR][nC]: the next free list position of every (bucket, chunk)
+__global__ __launch_bounds__(kBlock) void k_inv_fill(InvArgs a, int nR, int brows, int* cursor, int* list) {
     __shared__ int s_hist[kInvHist];
     const int bg = blockIdx.y, n0 = blockIdx.x * kInvRows, tid = threadIdx.x;
     const int nC = a.L / kChunk, R = n0 / brows;
     const bool lds = nC <= kInvHist;
-    int* gcur = cursor + (size_t)bg * nC * nR;
-    const int* off = boff + (size_t)bg * (nC * nR + 1);
+    int* gcur = cursor + (size_t)bg * nC * nR + (size_t)R * nC;
     int* lst = list + (size_t)bg * a.N * a.K;
     const int rows = min(kInvRows, a.N - n0);
     if (lds) {
         for (int c = tid; c < nC; c += kBlock) s_hist[c] = 0;
         __syncthreads();
-        for (int e = tid; e < rows * a.K; e += kBlock) {
-            const int n = n0 + e / a.K, slot = e % a.K;
-            int c;
-            if (entry_valid(a, a.idx + ((size_t)bg * a.Nrow + a.n0 + n) * a.K, slot, n, &c)) atomicAdd(&s_hist[c], 1);
-        }
+        for_entries(a, bg, n0, rows, [&](int c, int) { atomicAdd(&s_hist[c], 1); });
         __syncthreads();
         // reserve this block's range of every chunk it touches; s_hist becomes the running position
         for (int c = tid; c < nC; c += kBlock)
-            if (s_hist[c]) s_hist[c] = off[c * nR + R] + atomicAdd(&gcur[R * nC + c], s_hist[c]);
+            if (s_hist[c]) s_hist[c] = atomicAdd(&gcur[c], s_hist[c]);
         __syncthreads();
     }
-    for (int e = tid; e < rows * a.K; e += kBlock) {
-        const int n = n0 + e / a.K, slot = e % a.K;
-        int c;
-        if (!entry_valid(a, a.idx + ((size_t)bg * a.Nrow + a.n0 + n) * a.K, slot, n, &c)) continue;
-        const int pos = lds ? atomicAdd(&s_hist[c], 1) : off[c * nR + R] + atomicAdd(&gcur[R * nC + c], 1);
-        lst[pos] = (n << 6) | slot;
-    }
+    for_entries(a, bg, n0, rows, [&](int c, int ent) {
+        const int pos = lds ? atomicAdd(&s_hist[c], 1) : atomicAdd(&gcur[c], 1);
+        lst[pos] = ent;
+    });
 }
 
-// Exclusive prefix sum of one int per thread over a kBlock-thread block (wave
+// Exclusive prefix sum of one int per thread over a kScan-thread block (wave
 // scans by shuffles, then the wave totals); every thread gets the block total.
 // Contains barriers: called by every thread of the block.
+constexpr int kScan = 1024;
 __device__ __forceinline__ int block_exclusive_scan(int x, int* s_wave, int* total) {
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     int incl = x;
@@ -123,7 +131,7 @@ __device__ __forceinline__ int block_exclusive_scan(int x, int* s_wave, int* tot
     __syncthreads();
     int before = 0, all = 0;
 #pragma unroll
-    for (int i = 0; i < kBlock / kWave; ++i) {
+    for (int i = 0; i < kScan / kWave; ++i) {
         const int t = s_wave[i];
         before += i < w ? t : 0;
         all += t;
@@ -133,30 +141,55 @@ __device__ __forceinline__ int block_exclusive_scan(int x, int* s_wave, int* tot
     return before + incl - x;
 }
 
-// one block per (b, g): exclusive scan of the nR x nC counts in chunk-major order
-// into boff[nC * nR + 1], and each chunk's whole list into offsets[nC + 1]
-__global__ __launch_bounds__(kBlock) void k_inv_scan(const int* counts, int* boff, int* offsets, int nC, int nR) {
-    __shared__ int s_part[kBlock / kWave];
+// One block per (b, g): from the nR x nC counts, in chunk-major order, the sub-lists'
+// starts boff[nC * nR + 1] and each chunk's whole list offsets[nC + 1]; in the counts' own
+// bucket-major order the fill's cursors and (work != null) the work items, one block of the
+// chunk pass each: the (chunk, bucket) sub-lists cut into segments of kInvSeg entries, so
+// that the items in flight together work on one range of rows.  Both orders read the
+// counts from LDS while they fit (48 KB: 12288 of them; two launches of 256 threads
+// striding through global memory took 43 us at 8192 counts, 32K tokens).
+constexpr int kScanCounts = 12288;
+__global__ __launch_bounds__(kScan) void k_inv_scan(const int* counts, int* boff, int* offsets, int* cursor, int nC,
+                                                    int nR, size_t max_work_bg, int4* work, int* nwork) {
+    extern __shared__ int s_cnt[];
+    __shared__ int s_part[kScan / kWave];
     const int bg = blockIdx.x, tid = threadIdx.x;
     const int M = nC * nR;
-    const int per = (M + kBlock - 1) / kBlock;
-    const int lo = min(M, tid * per), hi = min(M, lo + per);
     const int* cnt = counts + (size_t)bg * M;
     int* bo = boff + (size_t)bg * (M + 1);
     int* off = offsets + (size_t)bg * (nC + 1);
-    int sum = 0;
-    auto count = [&](int i) { return cnt[(i % nR) * nC + i / nR]; };  // i = c * nR + R
-    for (int i = lo; i < hi; ++i) sum += count(i);
-    int total;
+    int* cur = cursor + (size_t)bg * M;
+    if (M <= kScanCounts) {
+        for (int i = tid; i < M; i += kScan) s_cnt[i] = cnt[i];
+        __syncthreads();
+        cnt = s_cnt;
+    }
+    const int per = (M + kScan - 1) / kScan;
+    const int lo = min(M, tid * per), hi = min(M, lo + per);
+    int total, sum = 0;
+    for (int i = lo; i < hi; ++i) sum += cnt[(i % nR) * nC + i / nR];  // i = c * nR + R
     int run = block_exclusive_scan(sum, s_part, &total);
     if (tid == 0) {
         bo[M] = total;
         off[nC] = total;
     }
     for (int i = lo; i < hi; ++i) {
+        const int c = i / nR, j = (i % nR) * nC + c;
         bo[i] = run;
-        if (i % nR == 0) off[i / nR] = run;
-        run += count(i);
+        cur[j] = run;
+        if (i % nR == 0) off[c] = run;
+        run += cnt[j];
+    }
+    if (!work) return;
+    int4* wk = work + (size_t)bg * max_work_bg;
+    sum = 0;
+    for (int i = lo; i < hi; ++i) sum += (cnt[i] + kInvSeg - 1) / kInvSeg;  // i = R * nC + c
+    run = block_exclusive_scan(sum, s_part, &total);
+    if (tid == 0) nwork[bg] = total;
+    for (int i = lo; i < hi; ++i) {
+        const int ns = (cnt[i] + kInvSeg - 1) / kInvSeg;
+        for (int sgi = 0; sgi < ns; ++sgi) wk[run + sgi] = make_int4(i / nC, i % nC, sgi, 0);
+        run += ns;
     }
 }
 
@@ -189,35 +222,7 @@ InvLayout inv_layout(int B, int Hkv, int N, int L, int K, size_t base, int row_e
     return w;
 }
 
-// Work items of one (b, g) (one block each): its (chunk, bucket) sub-lists cut into
-// segments of kInvSeg entries, bucket-major, so that the items in flight together
-// work on one range of rows.
-__global__ __launch_bounds__(kBlock) void k_inv_work(const int* boff, int nC, int nR, size_t max_work_bg, int4* work,
-                                                     int* nwork) {
-    __shared__ int s_part[kBlock / kWave];
-    const int bg = blockIdx.x, tid = threadIdx.x;
-    const int M = nC * nR;
-    const int* bo = boff + (size_t)bg * (M + 1);
-    int4* wk = work + (size_t)bg * max_work_bg;
-    const int per = (M + kBlock - 1) / kBlock;
-    const int lo = min(M, tid * per), hi = min(M, lo + per);
-    auto nseg = [&](int i) {  // i = R * nC + c
-        const int j = (i % nC) * nR + i / nC;
-        return (bo[j + 1] - bo[j] + kInvSeg - 1) / kInvSeg;
-    };
-    int sum = 0;
-    for (int i = lo; i < hi; ++i) sum += nseg(i);
-    int total;
-    int run = block_exclusive_scan(sum, s_part, &total);
-    if (tid == 0) nwork[bg] = total;
-    for (int i = lo; i < hi; ++i) {
-        const int ns = nseg(i);
-        for (int sgi = 0; sgi < ns; ++sgi) wk[run + sgi] = make_int4(i / nC, i % nC, sgi, 0);
-        run += ns;
-    }
-}
-
-void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStream_t s, bool work_list) {
+void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStream_t s, bool work_list, bool cleared) {
     char* base = static_cast<char*>(ws);
     int* counts = reinterpret_cast<int*>(base + w.counts);
     int* offsets = reinterpret_cast<int*>(base + w.offsets);
@@ -225,19 +230,18 @@ void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStr
     int* cursor = reinterpret_cast<int*>(base + w.cursor);
     int* list = reinterpret_cast<int*>(base + w.list);
     const int nC = a.L / kChunk;
-    const size_t ncnt = (size_t)a.B * a.Hkv * nC * w.nR;
-    const unsigned gc = (unsigned)((ncnt + kBlock - 1) / kBlock);
     const dim3 grows((a.N + kInvRows - 1) / kInvRows, a.B * a.Hkv);
-    HILS_LAUNCH("k_fill_i32", k_fill_i32, dim3(gc), dim3(kBlock), 0, s, counts, ncnt, 0);
-    HILS_LAUNCH("k_fill_i32", k_fill_i32, dim3(gc), dim3(kBlock), 0, s, cursor, ncnt, 0);
+    if (!cleared) {
+        const size_t ncnt = inv_count_words(a.B, a.Hkv, a.L, w);
+        HILS_LAUNCH("k_fill_i32", k_fill_i32, dim3((unsigned)((ncnt + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, counts,
+                    ncnt, 0);
+    }
     HILS_LAUNCH("k_inv_count", k_inv_count, grows, dim3(kBlock), 0, s, a, w.nR, w.brows, counts);
-    HILS_LAUNCH("k_inv_scan", k_inv_scan, dim3(a.B * a.Hkv), dim3(kBlock), 0, s, (const int*)counts, boff, offsets,
-                nC, w.nR);
-    HILS_LAUNCH("k_inv_fill", k_inv_fill, grows, dim3(kBlock), 0, s, a, w.nR, w.brows, (const int*)boff, cursor,
-                list);
-    if (work_list)
-        HILS_LAUNCH("k_inv_work", k_inv_work, dim3(a.B * a.Hkv), dim3(kBlock), 0, s, (const int*)boff, nC, w.nR,
-                    w.max_work_bg, reinterpret_cast<int4*>(base + w.work), reinterpret_cast<int*>(base + w.nwork));
+    const size_t M = (size_t)nC * w.nR;
+    HILS_LAUNCH("k_inv_scan", k_inv_scan, dim3(a.B * a.Hkv), dim3(kScan), M <= kScanCounts ? M * sizeof(int) : 0, s,
+                (const int*)counts, boff, offsets, cursor, nC, w.nR, w.max_work_bg,
+                work_list ? reinterpret_cast<int4*>(base + w.work) : nullptr, reinterpret_cast<int*>(base + w.nwork));
+    HILS_LAUNCH("k_inv_fill", k_inv_fill, grows, dim3(kBlock), 0, s, a, w.nR, w.brows, cursor, list);
 }
 
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t s) { return a.bf16 ? launch_bwd_mfma(a, s) : launch_bwd_f32(a, s); }

@@ -104,11 +104,13 @@ __device__ __forceinline__ bf16x8 pack_perm(const float* e0, const float* e1) {
 }
 
 // ---------------------------------------------------------------------------
-// u = dO . out: D/8 lanes per (row, head), 16 bytes of each per lane
+// u = dO . out: D/8 lanes per (row, head), 16 bytes of each per lane; also clears the
+// inverse index's counters, which the next launch uses
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_bwd_u(BwdArgs a, float* u) {
+__global__ __launch_bounds__(kBlock) void k_bwd_u(BwdArgs a, float* u, int* counts, size_t nclear) {
     constexpr int LPR = D / 8;  // lanes per row
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < nclear; i += (size_t)gridDim.x * kBlock) counts[i] = 0;
     const size_t rows = (size_t)a.B * a.Hq * a.N;
     const size_t r = (size_t)blockIdx.x * (kBlock / LPR) + threadIdx.x / LPR;
     const int d0 = (threadIdx.x % LPR) * 8;
@@ -809,9 +811,10 @@ struct BwRun {
         const int nC = a.L / kChunk;
         const size_t rows = (size_t)a.B * a.Hq * a.N;
         constexpr int upb = kBlock / (D / 8);  // rows per k_bwd_u block
-        HILS_LAUNCH("k_bwd_u", (k_bwd_u<D>), dim3((unsigned)((rows + upb - 1) / upb)), dim3(kBlock), 0, s, a, u);
+        HILS_LAUNCH("k_bwd_u", (k_bwd_u<D>), dim3((unsigned)((rows + upb - 1) / upb)), dim3(kBlock), 0, s, a, u,
+                    reinterpret_cast<int*>(ws + ly.inv.counts), inv_count_words(a.B, a.Hkv, a.L, ly.inv));
         const InvArgs ia{a.idx, a.B, a.Hkv, a.N, a.K, a.W, a.L, 0, a.N};
-        launch_inverse_index(ia, ly.inv, a.ws, s, false);
+        launch_inverse_index(ia, ly.inv, a.ws, s, false, true);
         launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
         if (a.q_route)
             HILS_LAUNCH("k_bwd_keys", (k_bwd_keys<D, G, true>), dim3(nC, a.Hkv, a.B), dim3(kKeyThreads), 0, s, a, offsets,

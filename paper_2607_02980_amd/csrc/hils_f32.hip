@@ -282,9 +282,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
 // ---------------------------------------------------------------------------
 // The forward's tile and split of the parts.  Per part S^T = K Q^T, GV^T = V dO^T, ds and
 // dq^T += K^T ds^T; a retrieved chunk adds ds^_c k'_c.  The waves' sums are added at the
-// end.  (One block per query with scalar dot products: 145 us at 2048 queries, 4 heads.)
+// end.  Also clears the inverse index's counters, which the next launch uses.  (One block
+// per query with scalar dot products: 145 us at 2048 queries, 4 heads.)
 template <int D, int G>
-__global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u) {
+__global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u, int* counts, size_t nclear) {
     constexpr int T = D / 16, DB = D / 16, NQ = kCols / G;
     __shared__ TileParts tp;
     __shared__ __align__(16) float s_o[kW][kCols][D + 4];
@@ -293,6 +294,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u)
     const int q0 = blockIdx.x * NQ, g = blockIdx.y, b = blockIdx.z;
     const int nC = a.L / kChunk;
     const size_t bg = (size_t)b * a.Hkv + g;
+    for (size_t i = (bg * gridDim.x + blockIdx.x) * kThreads + tid; i < nclear;
+         i += (size_t)gridDim.x * gridDim.y * gridDim.z * kThreads)
+        counts[i] = 0;
     const float* kb = as<float>(a.k) + bg * a.L * D;
     const float* vb = as<float>(a.v) + bg * a.L * D;
     const int hh = col % G, qi = col / G, n = min(q0 + qi, a.N - 1);
@@ -779,10 +783,10 @@ struct BwdRun {
         int* sorted = reinterpret_cast<int*>(ws + ly.sorted);
         const int nC = a.L / kChunk;
         const InvArgs ia{a.idx, a.B, a.Hkv, a.N, a.K, a.W, a.L, 0, a.N};
-        launch_inverse_index(ia, ly.inv, a.ws, s, false);
-        launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
         HILS_LAUNCH("k_bwd_dq_f32", (k_bwd_dq_f32<D, G>), dim3((a.N + NQ - 1) / NQ, a.Hkv, a.B), dim3(kThreads), 0, s,
-                    a, u);
+                    a, u, reinterpret_cast<int*>(ws + ly.inv.counts), inv_count_words(a.B, a.Hkv, a.L, ly.inv));
+        launch_inverse_index(ia, ly.inv, a.ws, s, false, true);
+        launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
         HILS_LAUNCH("k_bwd_keys_f32", (k_bwd_keys_f32<D, G>), dim3(nC * ly.nsplit, a.Hkv, a.B), dim3(kThreads), 0, s,
                     a, reinterpret_cast<const int*>(ws + ly.inv.offsets), (const int*)sorted, (const float*)u, sums,
                     ly.nsplit);

@@ -119,7 +119,11 @@ InvLayout inv_layout(int B, int Hkv, int N, int L, int K, size_t base, int row_e
 // at boff[c * nR + R]); offsets[c] .. offsets[c + 1] bound the whole list.
 // work_list = false skips the work items (consumers that walk whole lists do not
 // read them).
-void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStream_t s, bool work_list = true);
+// cleared: the counters (inv_count_words of them at w.counts) are 0 already.
+void launch_inverse_index(const InvArgs& a, const InvLayout& w, void* ws, hipStream_t s, bool work_list, bool cleared);
+inline size_t inv_count_words(int B, int Hkv, int L, const InvLayout& w) {
+    return (size_t)B * Hkv * (L / 64) * w.nR;
+}
 
 // Copies every (b, g, chunk) list of the index to `sorted` ([bg][N * K]) in ascending row
 // order, so that sums over a list have one order.

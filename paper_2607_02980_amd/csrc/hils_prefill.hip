@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kSW * kWave, NORM ? 3 : 4) void k_pf_score(FwdArgs 
     static_assert(NJ * kSW == NCB, "chunk blocks split evenly over the waves");
     __shared__ float s_sig[kSQ][kSL + 1];
     __shared__ int s_tid[kSW][64];
-    __shared__ float s_tsc[kSW][64];
+    __shared__ __align__(16) float s_tsc[kSW][64];
     __shared__ float s_lse[NORM ? G : 1][kSQ];
     extern __shared__ int s_dyn[];
     const int K = a.K;
@@ -538,13 +538,18 @@ __global__ __launch_bounds__(8 * kWave) void k_pf_sigma(FwdArgs a, float* sig) {
 // One wave per (row, KV group): the K best of sigma over the row's candidates
 // C_i (E registers of 64 candidates per lane, ids ascending over (register, lane)).
 constexpr int kSelWaves = 4;
+// It also clears the inverse index's counters (nclear words), which the next launch uses.
 template <int E>
-__global__ __launch_bounds__(kSelWaves * kWave) void k_pf_select(FwdArgs a, const float* sig) {
+__global__ __launch_bounds__(kSelWaves * kWave) void k_pf_select(FwdArgs a, const float* sig, int* counts,
+                                                                 size_t nclear) {
     __shared__ int s_tid[kSelWaves][kWave];
-    __shared__ float s_tsc[kSelWaves][kWave];
+    __shared__ __align__(16) float s_tsc[kSelWaves][kWave];
     __shared__ int s_oid[kSelWaves][kWave];
     __shared__ float s_osc[kSelWaves][kWave];
     const int w = wave_id(), lane = threadIdx.x % kWave;
+    for (size_t i = (size_t)blockIdx.x * (kSelWaves * kWave) + threadIdx.x; i < nclear;
+         i += (size_t)gridDim.x * (kSelWaves * kWave))
+        counts[i] = 0;
     const size_t r = (size_t)blockIdx.x * kSelWaves + w;  // (b, g, n) row
     if (r >= (size_t)a.B * a.Hkv * a.N) return;           // whole wave
     const int n = (int)(r % a.N);
@@ -1061,7 +1066,9 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 2) void k_pf_local(FwdArgs a, cons
             for (int db = 0; db < DB; ++db) {
                 f32x4 oc = mfma16x16x32(tr_operand_perm(tv, VROW, 0, db * 16, lane), pb0, zero4());
                 oc = mfma16x16x32(tr_operand_perm(tv, VROW, 32, db * 16, lane), pb1, oc);
-                o[db] = o[db] * rs + f * oc;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)  // (a chunk the row did not select may hold anything)
+                    o[db][i] = sel ? o[db][i] * rs + f * oc[i] : o[db][i];
                 if (db % 2 == 1) __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -1173,6 +1180,16 @@ struct PfRun {
         char* ws = static_cast<char*>(a.ws);
         bf16* part = reinterpret_cast<bf16*>(ws + ly.part);
         float* wgt = reinterpret_cast<float*>(ws + ly.wgt);
+        // Short sequences: with few more chunks than a row retrieves, a tile's union is
+        // hardly larger than one row's selection, and computing it beats the index, the
+        // records and three launches.  Attention of 2 x N tokens, 32 heads in groups of 4,
+        // d = 128, K = 16, chunk-major and union: 136 and 76 us at N = 1000 (16 chunks), 286
+        // and 179 at 2000 (32), 456 and 402 at 3001 (47), 401 and 396 at 4500 (71, one
+        // sequence); groups of 8 alike; groups of 1 (a wave packs 16 queries): 128 and 75 at
+        // 2000, 165 and 191 at 3001.  A given selection may have gaps, which the union does
+        // not look past: it stays chunk-major.
+        const bool few_chunks = !a.given_idx && !a.union_pack && a.L / kChunk <= (G == 1 ? 2 : 3) * a.K + 4;
+        bool cleared = false;  // the inverse index's counters
         if (!a.given_idx) {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);
             const size_t dyn = score_dyn_lds(a.K);
@@ -1193,16 +1210,19 @@ struct PfRun {
                 const size_t rows = (size_t)a.B * a.Hkv * a.N;
                 const dim3 rgr((unsigned)((rows + kSelWaves - 1) / kSelWaves));
                 const dim3 rbl(kSelWaves * kWave);
+                int* counts = reinterpret_cast<int*>(ws + ly.inv.counts);
+                const size_t nclear = few_chunks ? 0 : inv_count_words(a.B, a.Hkv, a.L, ly.inv);
+                cleared = nclear > 0;
                 if (nC <= kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<1>, rgr, rbl, 0, s, a, (const float*)sigma);
+                    HILS_LAUNCH("k_pf_select", k_pf_select<1>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
                 else if (nC <= 2 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<2>, rgr, rbl, 0, s, a, (const float*)sigma);
+                    HILS_LAUNCH("k_pf_select", k_pf_select<2>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
                 else if (nC <= 4 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<4>, rgr, rbl, 0, s, a, (const float*)sigma);
+                    HILS_LAUNCH("k_pf_select", k_pf_select<4>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
                 else if (nC <= 8 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<8>, rgr, rbl, 0, s, a, (const float*)sigma);
+                    HILS_LAUNCH("k_pf_select", k_pf_select<8>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
                 else
-                    HILS_LAUNCH("k_pf_select", k_pf_select<16>, rgr, rbl, 0, s, a, (const float*)sigma);
+                    HILS_LAUNCH("k_pf_select", k_pf_select<16>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
             } else if (a.head_norm) {
                 HILS_LAUNCH("k_pf_score", (k_pf_score<D, G, true>), grid, dim3(kSW * kWave), dyn, s, a);
             } else {
@@ -1210,7 +1230,7 @@ struct PfRun {
             }
         }
         const dim3 lgrid((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT, a.Hkv, a.B);
-        if (a.union_pack) {
+        if (a.union_pack || few_chunks) {
             // one-load-multiple-compute: no inverse index, no per-slot partials
             const int nC = a.L / kChunk;
             const int qk = LocalCfg<G>::QT * a.K;
@@ -1231,7 +1251,7 @@ struct PfRun {
         for (int n0 = 0; n0 < a.N; n0 += seg) {
             const int Ns = std::min(seg, a.N - n0);
             const InvArgs ia{a.idx, a.B, a.Hkv, Ns, a.K, a.W, a.L, n0, a.N};
-            launch_inverse_index(ia, ly.inv, a.ws, s);
+            launch_inverse_index(ia, ly.inv, a.ws, s, true, cleared && n0 == 0);
             if (a.q_route)
                 HILS_LAUNCH("k_pf_chunks", (k_pf_chunks<D, G, true>), cgrid, dim3(kBlock), 0, s, a, boff, ly.inv.nR,
                             list, work, ly.inv.max_work_bg, nwork, part, wgt, n0, Ns);

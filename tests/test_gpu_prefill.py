@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2607_02980_amd import synth
 from tests.gpu_helpers import (check_close, check_lse, check_selection, host_inputs, log, np32, oshape, to_device)
 
 pytestmark = pytest.mark.gpu
@@ -182,3 +183,37 @@ def test_prefill_is_deterministic():
     torch.cuda.synchronize()
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1075, 2, 4, 4, 0.97), (1330, 1, 8, 6, 0.0),
+                                           (770, 3, 1, 4, 0.0), (833, 3, 1, 4, 0.0), (1000, 2, 2, 64, 0.0)])
+def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
+    """Few more chunks than a row retrieves (the union path; on both sides of its limit,
+    3 K + 4 chunks or, groups of one, 2 K + 4) against the chunk-major pass, which a given
+    selection always takes; and a NaN value stays with the rows that attend it."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=2, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=64, topk=K, window=130)
+    host = host_inputs(p, 370, bias=True, route=True)
+    if rho:
+        host["q"] = synth.ar1_host(host["q"].shape, 371, "bf16", rho)
+    dev = to_device(host, p)
+
+    def run(flags, idx=None):
+        p.flags = flags
+        return hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"], dev["q_route"], idx=idx)
+
+    out, lse, idx = run(0)
+    ref, rlse, _ = run(hils.HILS_FLAG_GIVEN_IDX, idx.clone())
+    # the chunk-major records round each chunk's output to bf16 (2^-9), the union does not
+    assert (out.float() - ref.float()).abs().max() <= 2e-2 and (lse - rlse).abs().max() <= 2e-4
+    j = 200  # in chunk 3
+    dev["v"][0, 0, j] = float("nan")
+    n = torch.arange(N, device="cuda")
+    left = ((n - p.window + 1).div(64, rounding_mode="floor") * 64).clamp(min=0)
+    sees = ((n >= j) & (left <= j)) | (idx[0, 0] == j // 64).any(-1)
+    near = (n >= 128) & (left <= j + 192)  # a tile of up to 128 rows shares its windows' keys
+    out2, _, idx2 = run(0)
+    assert torch.equal(idx, idx2)
+    far = ~sees & ~near
+    assert torch.equal(out2[0, :G, far], out[0, :G, far]) and torch.isnan(out2[0, :G, sees]).all()
