@@ -291,19 +291,22 @@ __device__ inline int wave_topk_reg(const float (&sc)[E], const int (&id)[E], co
     uint32_t T = 0, id_thr = 0x7fffffffu;
     const bool all = (n <= K);
     constexpr bool kOrdered = FIRST != kTopkUnordered;
-    if (!all && E > 1) {
+    if (!all && (E > 1 || kOrdered)) {
         // Fast path.  The m-th largest of the lane maxima is a lower bound of the
         // m-th largest key (m lanes hold a key at least as large), and so is T0,
         // that bound with its low 16 bits cleared (found in 16 ballot steps), so
         // the m best entries are among the survivors key >= T0.  When they fit one
         // per lane they are compacted in visiting order and selected with
         // one-register passes.
-        uint32_t lmax = 0;
+        uint32_t T0 = 1u;  // (one register: every valid entry survives)
+        if constexpr (E > 1) {
+            uint32_t lmax = 0;
 #pragma unroll
-        for (int r = 0; r < E; ++r) lmax = key[r] > lmax ? key[r] : lmax;
-        uint32_t T0 = wave_kth_key<16>(lmax >> 16, m) << 16;
-        T0 = T0 ? T0 : 1u;
-        const int c = count_ge(T0);
+            for (int r = 0; r < E; ++r) lmax = key[r] > lmax ? key[r] : lmax;
+            T0 = wave_kth_key<16>(lmax >> 16, m) << 16;
+            T0 = T0 ? T0 : 1u;
+        }
+        const int c = E > 1 ? count_ge(T0) : n;
         if (c <= kWave) {
             int w = 0;
 #pragma unroll

@@ -35,6 +35,7 @@
 // so softmax rescaling is lane-local.  Per-slot partial vectors are stored in
 // the accumulators' lane order (store_lane_order).
 #include <atomic>
+#include <type_traits>
 
 #include "hils_device.hpp"
 #include "hils_dispatch.hpp"
@@ -537,8 +538,10 @@ __global__ __launch_bounds__(8 * kWave) void k_pf_sigma(FwdArgs a, float* sig) {
 
 // One wave per (row, KV group): the K best of sigma over the row's candidates
 // C_i (E registers of 64 candidates per lane, ids ascending over (register, lane)).
-constexpr int kSelWaves = 4;
 // It also clears the inverse index's counters (nclear words), which the next launch uses.
+// (Two or four rows per wave, all their scores in flight first: 138 against 135 us at 32K,
+// 18.6 against 15 us for 48K rows of 47 candidates: waves in flight hide the chains better.)
+constexpr int kSelWaves = 4;
 template <int E>
 __global__ __launch_bounds__(kSelWaves * kWave) void k_pf_select(FwdArgs a, const float* sig, int* counts,
                                                                  size_t nclear) {
@@ -766,7 +769,7 @@ struct LocalCfg {
 // bitmap over the chunks, then the set bits in order (dynamic LDS: the bitmap,
 // the rows' valid entries, the union list).
 template <int D, int G, bool UNION, bool ROUTE>
-__global__ __launch_bounds__(LocalCfg<G>::NT, 2) void k_pf_local(FwdArgs a, const bf16* part, const float* wgt, int n0,
+__global__ __launch_bounds__(LocalCfg<G>::NT, 4) void k_pf_local(FwdArgs a, const bf16* part, const float* wgt, int n0,
                                                                  int Ns) {
     using C = LocalCfg<G>;
     constexpr int KS = Tiles<D>::KS, DB = Tiles<D>::DB;
@@ -966,13 +969,12 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 2) void k_pf_local(FwdArgs a, cons
         }
         const int* myidx = s_idx + trow * a.K;
         int ptr = 0;
-        // Four union chunks in flight: chunk u is computed from LDS buffer u % 2 while
-        // chunks u + 1 .. u + 3 wait in a ring of registers (named slots, the loop
-        // unrolled four times, so that no register copy waits on a pending load) and
-        // chunk u + 4 is fetched into the slot chunk u + 1 leaves when it is staged.
-        // The chunk's G landmark rows and biases travel with its K/V (threads <
-        // G * D / 8).  Past the union's end the fetches re-read the last chunk (in
-        // bounds, never staged), so the loads are the same in every iteration.
+        // As the window's blocks: chunk u is computed from LDS buffer u % 2 while chunk u + 1
+        // is fetched into registers, one barrier per chunk.  At 128 VGPRs two workgroups
+        // share a CU and cover each other's barriers and chains (four chunks in flight in
+        // registers, at one workgroup per CU: 139 us for 2 x 3001 tokens, 16 heads in groups
+        // of 2, d = 64).  The chunk's G landmark rows and biases travel with its K/V
+        // (threads < G * D / 8).
         const bool lm_thread = tid < G * D / 8;
         const int lm_h = tid / (D / 8), lm_d8 = (tid % (D / 8)) * 8;
         const int lm_hl = (a.Hl == a.Hq) ? g * G + min(lm_h, G - 1) : g;
@@ -1072,30 +1074,14 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 2) void k_pf_local(FwdArgs a, cons
                 if (db % 2 == 1) __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // one step: fetch chunk u + 4 into `ld`, compute chunk u, stage chunk u + 1
-        // (held in `st`) into the other buffer
-        auto step = [&](int u, Slot& st, Slot& ld) {
-            ld = fetch_slot(u + 4);
-            compute(u);
-            if (u + 1 < U) stage_slot((u + 1) & 1, st);
-            __syncthreads();
-        };
-        Slot r0, r1, r2, r3;
-        if (U > 0) {
-            stage_slot(0, fetch_slot(0));
-            r1 = fetch_slot(1);
-            r2 = fetch_slot(2);
-            r3 = fetch_slot(3);
-        }
+        if (U > 0) stage_slot(0, fetch_slot(0));
         __syncthreads();
-        for (int u = 0; u < U; u += 4) {
-            step(u, r1, r0);
-            if (u + 1 >= U) break;
-            step(u + 1, r2, r1);
-            if (u + 2 >= U) break;
-            step(u + 2, r3, r2);
-            if (u + 3 >= U) break;
-            step(u + 3, r0, r3);
+        for (int u = 0; u < U; ++u) {
+            Slot nxt;
+            if (u + 1 < U) nxt = fetch_slot(u + 1);  // uniform over the block
+            compute(u);
+            if (u + 1 < U) stage_slot((u + 1) & 1, nxt);
+            __syncthreads();
         }
     } else {
     // the row's retrieved chunks: slots in idx order, valid entries only
@@ -1181,14 +1167,18 @@ struct PfRun {
         bf16* part = reinterpret_cast<bf16*>(ws + ly.part);
         float* wgt = reinterpret_cast<float*>(ws + ly.wgt);
         // Short sequences: with few more chunks than a row retrieves, a tile's union is
-        // hardly larger than one row's selection, and computing it beats the index, the
-        // records and three launches.  Attention of 2 x N tokens, 32 heads in groups of 4,
-        // d = 128, K = 16, chunk-major and union: 136 and 76 us at N = 1000 (16 chunks), 286
-        // and 179 at 2000 (32), 456 and 402 at 3001 (47), 401 and 396 at 4500 (71, one
-        // sequence); groups of 8 alike; groups of 1 (a wave packs 16 queries): 128 and 75 at
-        // 2000, 165 and 191 at 3001.  A given selection may have gaps, which the union does
-        // not look past: it stays chunk-major.
-        const bool few_chunks = !a.given_idx && !a.union_pack && a.L / kChunk <= (G == 1 ? 2 : 3) * a.K + 4;
+        // not much larger than one row's selection, and computing it beats the index, the
+        // records and three launches.  Attention with i.i.d. queries (like neighbours make the
+        // union smaller), d = 128, K = 16, 32 heads, chunk-major and union: groups of 4, 2 x
+        // 2000 tokens (32 chunks) 286 and 161 us, 3001 (47) 456 and 315, 1 x 4500 (71) 384 and
+        // 339, 6500 (102) 562 and 743; groups of 8, 4500: 445 and 324, 6500: 663 and 669;
+        // K = 32, 6500: 916 and 816; K = 4, 2000 (32): 143 and 141.  Narrower groups put more
+        // queries in a wave: groups of 2 (d = 64), 3001: 150 and 117, 4500: 122 and 129;
+        // groups of 1, 2000: 110 and 76, 3001: 137 and 148.  A given selection may have gaps,
+        // which the union does not look past: it stays chunk-major.
+        const int nC = a.L / kChunk;
+        const bool few_chunks =
+            !a.given_idx && !a.union_pack && nC <= (G == 1 ? 2 * a.K + 4 : G == 2 ? 3 * a.K + 4 : 4 * a.K + 8);
         bool cleared = false;  // the inverse index's counters
         if (!a.given_idx) {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);
@@ -1197,7 +1187,6 @@ struct PfRun {
                 const dim3 lgr((unsigned)((a.N + kLseRows - 1) / kLseRows), a.Hq, a.B);
                 HILS_LAUNCH("k_pf_lse", k_pf_lse<D>, lgr, dim3(8 * kWave), 0, s, a);
             }
-            const int nC = a.L / kChunk;
             if (nC <= 16 * kWave && !a.union_pack &&
                 (size_t)a.B * a.Hkv * a.N * nC * sizeof(float) <= ly.wgt - ly.part) {
                 // the split scorer: sigma in the records' area (see k_pf_sigma)
@@ -1208,21 +1197,24 @@ struct PfRun {
                 else
                     HILS_LAUNCH("k_pf_sigma", (k_pf_sigma<D, G, false>), sgr, dim3(8 * kWave), 0, s, a, sigma);
                 const size_t rows = (size_t)a.B * a.Hkv * a.N;
-                const dim3 rgr((unsigned)((rows + kSelWaves - 1) / kSelWaves));
-                const dim3 rbl(kSelWaves * kWave);
                 int* counts = reinterpret_cast<int*>(ws + ly.inv.counts);
                 const size_t nclear = few_chunks ? 0 : inv_count_words(a.B, a.Hkv, a.L, ly.inv);
                 cleared = nclear > 0;
+                auto select = [&](auto e_tag) {
+                    constexpr int E = decltype(e_tag)::value;
+                    HILS_LAUNCH("k_pf_select", k_pf_select<E>, dim3((unsigned)((rows + kSelWaves - 1) / kSelWaves)),
+                                dim3(kSelWaves * kWave), 0, s, a, (const float*)sigma, counts, nclear);
+                };
                 if (nC <= kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<1>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
+                    select(std::integral_constant<int, 1>{});
                 else if (nC <= 2 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<2>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
+                    select(std::integral_constant<int, 2>{});
                 else if (nC <= 4 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<4>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
+                    select(std::integral_constant<int, 4>{});
                 else if (nC <= 8 * kWave)
-                    HILS_LAUNCH("k_pf_select", k_pf_select<8>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
+                    select(std::integral_constant<int, 8>{});
                 else
-                    HILS_LAUNCH("k_pf_select", k_pf_select<16>, rgr, rbl, 0, s, a, (const float*)sigma, counts, nclear);
+                    select(std::integral_constant<int, 16>{});
             } else if (a.head_norm) {
                 HILS_LAUNCH("k_pf_score", (k_pf_score<D, G, true>), grid, dim3(kSW * kWave), dyn, s, a);
             } else {
@@ -1232,7 +1224,6 @@ struct PfRun {
         const dim3 lgrid((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT, a.Hkv, a.B);
         if (a.union_pack || few_chunks) {
             // one-load-multiple-compute: no inverse index, no per-slot partials
-            const int nC = a.L / kChunk;
             const int qk = LocalCfg<G>::QT * a.K;
             const size_t dyn = (size_t)((nC + 31) / 32 + qk + min(nC, qk)) * sizeof(int);
             if (a.q_route)

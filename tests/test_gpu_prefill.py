@@ -185,11 +185,12 @@ def test_prefill_is_deterministic():
         assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1075, 2, 4, 4, 0.97), (1330, 1, 8, 6, 0.0),
-                                           (770, 3, 1, 4, 0.0), (833, 3, 1, 4, 0.0), (1000, 2, 2, 64, 0.0)])
+@pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1530, 2, 4, 4, 0.97), (1540, 1, 4, 4, 0.0),
+                                           (1330, 1, 8, 6, 0.0), (770, 3, 1, 4, 0.0), (833, 3, 1, 4, 0.0),
+                                           (1024, 1, 2, 4, 0.0), (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0)])
 def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
-    """Few more chunks than a row retrieves (the union path; on both sides of its limit,
-    3 K + 4 chunks or, groups of one, 2 K + 4) against the chunk-major pass, which a given
+    """Few more chunks than a row retrieves (the union path; on both sides of its limits,
+    2 K + 4, 3 K + 4 and 4 K + 8 chunks for groups of 1, 2 and more) against the chunk-major pass, which a given
     selection always takes; and a NaN value stays with the rows that attend it."""
     from paper_2607_02980_amd import hils
 
