@@ -26,8 +26,9 @@ namespace hils {
 
 namespace {
 
-constexpr int kW = 4;                    // waves per block
+constexpr int kW = 4;                    // waves per block of the backward
 constexpr int kThreads = kW * kWave;
+constexpr int kAttnW = 8;                // waves per block of the forward
 constexpr int kCols = 16;                // (query, head) columns of a block: 16 / G queries x G heads
 constexpr int kMaxItems = kCols * 64;    // entries of 16 / G queries' selections (K <= 64)
 
@@ -44,15 +45,16 @@ struct TileParts {
     int sel[kMaxItems];               // [query][K] the rows' valid entries, else -1
     int chunk[kMaxItems];             // union, in order of (first query, slot)
     unsigned short users[kMaxItems];  // its queries, one bit each
-    int wave_n[kW];
+    int wave_n[kAttnW];
     int n;                            // union size
     int bad;                          // a result of the tile is not finite
 };
 
 // Fills sel, chunk, users and n; called by the whole block, ends with a barrier.
+template <int NW>
 __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int K, int W, int q0, int nq) {
     const int tid = threadIdx.x, lane = tid % kWave, w = wave_id();
-    for (int e = tid; e < nq * K; e += kThreads) {
+    for (int e = tid; e < nq * K; e += NW * kWave) {
         const int n = q0 + e / K;
         int v = -1;
         if (n < N) {
@@ -64,7 +66,7 @@ __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int
     if (tid == 0) tp.bad = 0;
     __syncthreads();
     int base = 0;
-    for (int e0 = 0; e0 < nq * K; e0 += kThreads) {
+    for (int e0 = 0; e0 < nq * K; e0 += NW * kWave) {
         const int e = e0 + tid;
         const int c = e < nq * K ? tp.sel[e] : -1;
         unsigned users = 0;
@@ -79,7 +81,7 @@ __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int
         __syncthreads();
         int pos = base + popc64(bal & ((1ull << lane) - 1ull));
         int all = 0;
-        for (int i = 0; i < kW; ++i) {
+        for (int i = 0; i < NW; ++i) {
             pos += i < w ? tp.wave_n[i] : 0;
             all += tp.wave_n[i];
         }
@@ -94,17 +96,83 @@ __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int
     __syncthreads();
 }
 
-// q^ . k' of the lane's column: its row operand's dims, summed over the lane groups.
+// x . y of two rows, the lane's dims (both pointers at dim 4 lg), summed over the lane groups.
 template <int D>
-__device__ __forceinline__ float row_dot(const f32x4* x, const float* row, int lg) {
+__device__ __forceinline__ float row_dot(const float* x, const float* y) {
     float acc = 0.f;
 #pragma unroll
     for (int t = 0; t < D / 16; ++t) {
-        const f32x4 y = ld4(row + 16 * t + 4 * lg);
+        const f32x4 u = ld4(x + 16 * t), v = ld4(y + 16 * t);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = fmaf(x[t][j], y[j], acc);
+        for (int j = 0; j < 4; ++j) acc = fmaf(u[j], v[j], acc);
     }
     return group4_sum(acc);
+}
+
+// A 64-row block of X as row operands (16 rows k, k-steps t) or as column operands
+// (rows 16 k + 4 lg + i, 64-wide dim block dd), in registers: 64 or, d = 128, 128 of them.
+template <int D>
+struct RowOps {
+    f32x4 x[4][D / 16];
+    __device__ __forceinline__ void load(const float* X, int lane) {
+        const float* p = X + (size_t)(lane % 16) * D + 4 * (lane / 16);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int t = 0; t < D / 16; ++t) x[k][t] = ld4(p + (size_t)16 * k * D + 16 * t);
+    }
+    // acc[k][row 16 k + 4 lg + i][column l%16] of the block against the columns' y
+    __device__ __forceinline__ void times(const f32x4* y, f32x4* acc) const {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = zero4();
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[k] = mfma_f32(x[k][t][j], y[t][j], acc[k]);
+    }
+};
+template <int D>
+struct ColOps {
+    f32x4 x[4][4][D / 64];
+    __device__ __forceinline__ void load(const float* X, int lane) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int dd = 0; dd < D / 64; ++dd)
+                    x[k][i][dd] = ld4(X + (size_t)(16 * k + 4 * (lane / 16) + i) * D + 64 * dd + 4 * (lane % 16));
+    }
+    // o[dims][column] += X^T p; rows at or past `rows` count as zero (their bytes may be
+    // anything, and 0 * NaN would reach every column)
+    __device__ __forceinline__ void add(int rows, const f32x4* p, f32x4* o, int lane) {
+        if (rows < kChunk) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int dd = 0; dd < D / 64; ++dd)
+                        if (16 * k + 4 * (lane / 16) + i >= rows) x[k][i][dd] = zero4();
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int dd = 0; dd < D / 64; ++dd)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o[4 * dd + j] = mfma_f32(x[k][i][dd][j], p[k][i], o[4 * dd + j]);
+    }
+};
+
+// The items of a wave's tile: pieces 0 .. npiece - 1, then the union's chunks; the first
+// one from `it` on (in steps of the waves) that a query of `mine` uses.
+__device__ __forceinline__ int next_item(const TileParts& tp, int it, int npiece, int items, unsigned mine) {
+    while (it >= npiece && it < items && (__builtin_amdgcn_readfirstlane(tp.users[it - npiece]) & mine) == 0u) it += kW;
+    return it;
 }
 
 // acc[key 4 lg + i][column l%16] of 16 rows of X (from `row0`) against the columns' x.
@@ -152,11 +220,11 @@ __device__ __forceinline__ void add_columns(const float* row0, int rows, const f
 // waves per SIMD in short sequences.  2048 queries, 4 heads over 1 KV head, d = 64,
 // K = 4: one block per query with scalar dot products from LDS took 119 us.
 template <int D, int G>
-__global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
+__global__ __launch_bounds__(kAttnW * kWave, D == 64 ? 4 : 2) void k_attn_f32(FwdArgs a) {
     constexpr int T = D / 16, DB = D / 16, NQ = kCols / G;
     __shared__ TileParts tp;
-    __shared__ __align__(16) float s_o[kW][kCols][D + 4];
-    __shared__ float s_m[kW][kCols], s_z[kW][kCols];
+    __shared__ __align__(16) float s_o[kAttnW][kCols][D + 4];
+    __shared__ float s_m[kAttnW][kCols], s_z[kAttnW][kCols];
     const int tid = threadIdx.x, w = wave_id(), lane = tid % kWave, lg = lane / 16, col = lane % 16;
     const int q0 = blockIdx.x * NQ, g = blockIdx.y, b = blockIdx.z;
     const int nC = a.L / kChunk;
@@ -168,13 +236,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
     const size_t row = ((size_t)b * a.Hq + g * G + hh) * a.N + n;
     const float* lrows = as<float>(a.lmk) + ((size_t)b * a.Hl + hl) * nC * D;
     const float* lbias = a.bias ? a.bias + ((size_t)b * a.Hl + hl) * nC : nullptr;
-    f32x4 q[T], qr[T];
+    f32x4 q[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        q[t] = ld4(as<float>(a.q) + row * D + 16 * t + 4 * lg);
-        qr[t] = a.q_route ? ld4(as<float>(a.q_route) + row * D + 16 * t + 4 * lg) : q[t];
-    }
-    build_parts(tp, a.idx + bg * a.N * a.K, a.N, a.K, a.W, q0, NQ);
+    for (int t = 0; t < T; ++t) q[t] = ld4(as<float>(a.q) + row * D + 16 * t + 4 * lg);
+    const float* qrow = as<float>(a.q_route ? a.q_route : a.q) + row * D + 4 * lg;
+    build_parts<kAttnW>(tp, a.idx + bg * a.N * a.K, a.N, a.K, a.W, q0, NQ);
 
     // one pass over the parts of the queries first .. last; writes those rows
     auto pass = [&](int first, int last) {
@@ -187,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
         for (int db = 0; db < DB; ++db) o[db] = zero4();
         float M = -INFINITY, Z = 0.f;
         const int items = npiece + __builtin_amdgcn_readfirstlane(tp.n);  // scalar: MFMAs ignore the lane mask
-        for (int it = w; it < items; it += kW) {
+        for (int it = w; it < items; it += kAttnW) {
             const bool piece = it < npiece;
             const unsigned users =
                 piece ? 0u : __builtin_amdgcn_readfirstlane(tp.users[piece ? 0 : it - npiece]) & mine;
@@ -221,7 +287,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
             l = group4_sum(l);
             // the part's logit (log of the mass it enters with) and the factor of its exponentials
             const bool on = piece ? mx != -INFINITY : (users >> qi) & 1u;
-            const float z = piece ? mx : a.scale * row_dot<D>(qr, lrows + (size_t)c * D, lg) + (lbias ? lbias[c] : 0.f);
+            const float z = piece ? mx : a.scale * row_dot<D>(qrow, lrows + (size_t)c * D + 4 * lg) + (lbias ? lbias[c] : 0.f);
             const float Mn = on ? fmaxf(M, z) : M;
             const float Mu = Mn == -INFINITY ? 0.f : Mn;
             const float rs = fexp(M - Mu);
@@ -229,14 +295,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
             Z = Z * rs + (piece ? l * e : e);
             const float f = piece ? e : e / l;
             M = Mn;
+            f32x4 oc[DB];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int db = 0; db < DB; ++db) oc[db] = zero4();
 #pragma unroll
-                for (int i = 0; i < 4; ++i) s[k][i] = on ? s[k][i] * f : 0.f;
+            for (int k = 0; k < 4; ++k) add_columns<D>(vc + 16 * k * D, nlast + 1 - j0 - 16 * k, s[k], oc, lane);
 #pragma unroll
-            for (int db = 0; db < DB; ++db) o[db] *= rs;
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) add_columns<D>(vc + 16 * k * D, nlast + 1 - j0 - 16 * k, s[k], o, lane);
+                for (int i = 0; i < 4; ++i) o[db][i] = on ? o[db][i] * rs + f * oc[db][i] : o[db][i];
         }
         if (lg == 0) {
             s_m[w][col] = M;
@@ -249,16 +316,16 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
                 st4(&s_o[w][col][64 * dd + 16 * lg + 4 * i],
                     f32x4{o[4 * dd][i], o[4 * dd + 1][i], o[4 * dd + 2][i], o[4 * dd + 3][i]});
         __syncthreads();
-        for (int e = tid; e < kCols * D / 4; e += kThreads) {
+        for (int e = tid; e < kCols * D / 4; e += (kAttnW * kWave)) {
             const int cc = e / (D / 4), d4 = (e % (D / 4)) * 4, qq = cc / G, nn = q0 + qq;
             if (nn >= a.N || qq < first || qq > last) continue;
             float mm = s_m[0][cc];
 #pragma unroll
-            for (int i = 1; i < kW; ++i) mm = fmaxf(mm, s_m[i][cc]);
+            for (int i = 1; i < kAttnW; ++i) mm = fmaxf(mm, s_m[i][cc]);
             float zz = 0.f;
             f32x4 acc = zero4();
 #pragma unroll
-            for (int i = 0; i < kW; ++i) {
+            for (int i = 0; i < kAttnW; ++i) {
                 const float x = fexp(s_m[i][cc] - mm);
                 zz += s_z[i][cc] * x;
                 acc += ld4(&s_o[i][cc][d4]) * x;
@@ -285,7 +352,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_f32(FwdArgs a) {
 // end.  Also clears the inverse index's counters, which the next launch uses.  (One block
 // per query with scalar dot products: 145 us at 2048 queries, 4 heads.)
 template <int D, int G>
-__global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u, int* counts, size_t nclear) {
+__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_dq_f32(BwdArgs a, float* u, int* counts, size_t nclear) {
     constexpr int T = D / 16, DB = D / 16, NQ = kCols / G;
     __shared__ TileParts tp;
     __shared__ __align__(16) float s_o[kW][kCols][D + 4];
@@ -305,12 +372,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u,
     const float* lrows = as<float>(a.lmk) + ((size_t)b * a.Hl + hl) * nC * D;
     const float* lbias = a.bias ? a.bias + ((size_t)b * a.Hl + hl) * nC : nullptr;
     const bool route = a.q_route != nullptr;
-    f32x4 q[T], qr[T], go[T];
+    const float* qrow = as<float>(route ? a.q_route : a.q) + row * D + 4 * lg;
+    f32x4 q[T], go[T];
     float ub = 0.f;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         q[t] = ld4(as<float>(a.q) + row * D + 16 * t + 4 * lg);
-        qr[t] = route ? ld4(as<float>(a.q_route) + row * D + 16 * t + 4 * lg) : q[t];
         go[t] = ld4(as<float>(a.dout) + row * D + 16 * t + 4 * lg);
         const f32x4 y = ld4(as<float>(a.out) + row * D + 16 * t + 4 * lg);
 #pragma unroll
@@ -319,7 +386,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u,
     ub = group4_sum(ub);
     const float L = a.lse[row];
     if (w == 0 && lg == 0 && q0 + qi < a.N) u[row] = ub;
-    build_parts(tp, a.idx + bg * a.N * a.K, a.N, a.K, a.W, q0, NQ);
+    build_parts<kW>(tp, a.idx + bg * a.N * a.K, a.N, a.K, a.W, q0, NQ);
 
     auto pass = [&](int first, int last) {
         const int nlast = min(q0 + last, a.N - 1);
@@ -330,21 +397,27 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u,
 #pragma unroll
         for (int db = 0; db < DB; ++db) dq[db] = dr[db] = zero4();
         const int items = npiece + __builtin_amdgcn_readfirstlane(tp.n);  // scalar: MFMAs ignore the lane mask
-        for (int it = w; it < items; it += kW) {
+        auto chunk_of = [&](int i) {
+            return __builtin_amdgcn_readfirstlane(i < npiece ? c0 + i : tp.chunk[max(i - npiece, 0)]);
+        };
+        int it = next_item(tp, w, npiece, items, mine);
+        int c = it < items ? chunk_of(it) : 0;
+        while (it < items) {
             const bool piece = it < npiece;
-            const unsigned users =
-                piece ? 0u : __builtin_amdgcn_readfirstlane(tp.users[piece ? 0 : it - npiece]) & mine;
-            if (!piece && users == 0u) continue;  // uniform over the wave
-            const int c = __builtin_amdgcn_readfirstlane(piece ? c0 + it : tp.chunk[piece ? 0 : it - npiece]);
-            const float* kc = kb + (size_t)c * kChunk * D;
-            const float* vc = vb + (size_t)c * kChunk * D;
+            const unsigned users = piece ? 0u : __builtin_amdgcn_readfirstlane(tp.users[max(it - npiece, 0)]);
             const int j0 = c * kChunk;
+            // V's rows in flight during S, K's columns during the softmax terms
+            RowOps<D> kr, vr;
+            kr.load(kb + (size_t)j0 * D, lane);
+            vr.load(vb + (size_t)j0 * D, lane);
             f32x4 s[4], gv[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                s[k] = rows_times<D>(kc + 16 * k * D, q, lane);
-                gv[k] = rows_times<D>(vc + 16 * k * D, go, lane);
-            }
+            kr.times(q, s);
+            vr.times(go, gv);
+            __builtin_amdgcn_sched_barrier(0);
+            ColOps<D> kc;
+            kc.load(kb + (size_t)j0 * D, lane);
+            const int nit = next_item(tp, it + kW, npiece, items, mine);
+            const int cn = nit < items ? chunk_of(nit) : c;
             if (piece) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
@@ -383,7 +456,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u,
                     }
                 uc = group4_sum(uc);
                 const float* lrow = lrows + (size_t)c * D;
-                const float sh = a.scale * row_dot<D>(qr, lrow, lg) + (lbias ? lbias[c] : 0.f);
+                const float sh = a.scale * row_dot<D>(qrow, lrow + 4 * lg) + (lbias ? lbias[c] : 0.f);
                 const float al = fexp(sh - L);
                 const float dsh = on ? al * (uc - ub) : 0.f;
 #pragma unroll
@@ -399,8 +472,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_bwd_dq_f32(BwdArgs a, float* u,
                         for (int j = 0; j < 4; ++j) dr[4 * dd + j][i] += on ? dsh * y[j] : 0.f;
                     }
             }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) add_columns<D>(kc + 16 * k * D, nlast + 1 - j0 - 16 * k, s[k], dq, lane);
+            kc.add(nlast + 1 - j0, s, dq, lane);
+            it = nit;
+            c = cn;
         }
 #pragma unroll
         for (int dd = 0; dd < D / 64; ++dd)
@@ -532,10 +606,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
                 y[k] = ld4(go + r * D + 16 * k + 4 * lg);
             }
             if (ret) {
-                f32x4 z[T];
-#pragma unroll
-                for (int k = 0; k < T; ++k) z[k] = route ? ld4(qr + r * D + 16 * k + 4 * lg) : x[k];
-                sh_row = a.scale * row_dot<D>(z, lrow, lg) + lbias;
+                sh_row = a.scale * row_dot<D>(qr + r * D + 4 * lg, lrow + 4 * lg) + lbias;
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -766,7 +837,8 @@ struct AttnRun {
     template <int D, int G>
     static hipError_t run(const FwdArgs& a, hipStream_t s) {
         constexpr int NQ = kCols / G;
-        HILS_LAUNCH("k_attn_f32", (k_attn_f32<D, G>), dim3((a.N + NQ - 1) / NQ, a.Hkv, a.B), dim3(kThreads), 0, s, a);
+        HILS_LAUNCH("k_attn_f32", (k_attn_f32<D, G>), dim3((a.N + NQ - 1) / NQ, a.Hkv, a.B), dim3(kAttnW * kWave), 0, s,
+                    a);
         return hipGetLastError();
     }
 };
