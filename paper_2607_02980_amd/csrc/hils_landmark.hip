@@ -192,11 +192,17 @@ template <int D>
 struct LmkWaveSmem {
     bf16 k[kChunk * (D + 16)];  // the chunk's keys, row-major (K^T operands)
 };
+// The operands of the dK product take K's place once dq' is formed: 18 KB instead of 33,
+// so that 8 of these one-wave workgroups share a CU (4: 46 us at 32K keys, 32 heads).
 template <int D>
-struct LmkWaveSmemB {
-    bf16 k[kChunk * (D + 16)];
+struct LmkDkOps {
     bf16 t[kChunk * 40];        // [key][p hi | p lo | scale ds hi | scale ds lo] x 8 heads (+8 pad)
-    bf16 r[32 * (D + 16)];      // [dk' ; dk' ; q' ; q'] x 8 heads, row-major (B operands of dK)
+    bf16 r[32 * (D + 16)];      // [dk' ; dk' ; q' ; q'] x 8 heads, row-major
+};
+template <int D>
+union LmkWaveSmemB {
+    bf16 k[kChunk * (D + 16)];
+    LmkDkOps<D> o;
 };
 
 // operand pair of P^T in the permuted key order of two S^T blocks, split hi / lo
@@ -327,18 +333,6 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
     const bf16* kg = as<bf16>(a.k) + (((size_t)b * a.Hkv + g) * a.L + (size_t)c * kChunk) * D;
     const bf16* qrow = as<bf16>(a.lq) + (a.shared ? (size_t)hl : row) * D;
     const bf16* dkrow = as<bf16>(a.dlmk) + row * D;
-    // B rows of the dK product: dk' of head m in rows m and 8 + m, q' in 16 + m and
-    // 24 + m (zero for m >= nlh)
-    for (int e = lane; e < 32 * D / 8; e += kWave) {
-        const int rr = e / (D / 8), d8 = (e % (D / 8)) * 8, m = rr % 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (m < nlh) {
-            const size_t rm = ((size_t)b * a.Hl + g * nlh + m) * nC + c;
-            v = rr < 16 ? *reinterpret_cast<const uint4*>(as<bf16>(a.dlmk) + rm * D + d8)
-                        : *reinterpret_cast<const uint4*>(as<bf16>(a.lq) + (a.shared ? (size_t)(g * nlh + m) : rm) * D + d8);
-        }
-        *reinterpret_cast<uint4*>(sm.r + rr * VROW + d8) = v;
-    }
     f32x4 p[4];
     float lse, ps;
     lmk_softmax<D>(a, kg, qrow, hv, sm.k, p, lse, ps);
@@ -388,6 +382,25 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
                     pack_bf16x2(a.scale * o[d][0], a.scale * o[d][1]), pack_bf16x2(a.scale * o[d][2], a.scale * o[d][3]));
         }
     }
+    // K's tile is read; rows of the dK product into it: dk' of head m in rows m and 8 + m,
+    // q' in 16 + m and 24 + m (zero for m >= nlh), again from L2
+    uint4 rv[32 * D / 8 / kWave];
+#pragma unroll
+    for (int u = 0; u < 32 * D / 8 / kWave; ++u) {
+        const int e = lane + u * kWave, rr = e / (D / 8), d8 = (e % (D / 8)) * 8, m = rr % 8;
+        const size_t rm = ((size_t)b * a.Hl + g * nlh + min(m, nlh - 1)) * nC + c;
+        const bf16* src = rr < 16 ? as<bf16>(a.dlmk) + rm * D
+                                  : as<bf16>(a.lq) + (a.shared ? (size_t)(g * nlh + min(m, nlh - 1)) : rm) * D;
+        const uint4 v = *reinterpret_cast<const uint4*>(src + d8);
+        rv[u] = m < nlh ? v : make_uint4(0, 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int u = 0; u < 32 * D / 8 / kWave; ++u) {
+        const int e = lane + u * kWave;
+        *reinterpret_cast<uint4*>(sm.o.r + e / (D / 8) * VROW + (e % (D / 8)) * 8) = rv[u];
+    }
     // T[key][..]: p hi, p lo, scale ds hi, scale ds lo of head n16 (lanes n16 < 8)
     if (n16 < 8) {
 #pragma unroll
@@ -397,24 +410,38 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
                 const int key = kb * 16 + lg * 4 + i;
                 const float pv = hv ? p[kb][i] : 0.f, dv = hv ? a.scale * ds[kb][i] : 0.f;
                 const bf16 ph = from_f32<bf16>(pv), dh = from_f32<bf16>(dv);
-                sm.t[key * TROW + n16] = ph;
-                sm.t[key * TROW + 8 + n16] = from_f32<bf16>(pv - to_f32(ph));
-                sm.t[key * TROW + 16 + n16] = dh;
-                sm.t[key * TROW + 24 + n16] = from_f32<bf16>(dv - to_f32(dh));
+                sm.o.t[key * TROW + n16] = ph;
+                sm.o.t[key * TROW + 8 + n16] = from_f32<bf16>(pv - to_f32(ph));
+                sm.o.t[key * TROW + 16 + n16] = dh;
+                sm.o.t[key * TROW + 24 + n16] = from_f32<bf16>(dv - to_f32(dh));
             }
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // dK[key][dim] = sum_m p_m,key dk'_m + scale ds_m,key q'_m (lane: keys 4 lg + i, dim n16)
+    // dK^T[dim][key] = sum_m dk'_m p_m,key + q'_m scale ds_m,key, dims taken so that a lane's
+    // accumulators of two products are 8 neighbouring dims of its key n16 (dim 32 d + 8 lg +
+    // 4 h + i: 16-byte stores; as [key][dim] a lane held 4 keys and stored 2 bytes at a time)
     bf16* dkb = as_mut<bf16>(a.dk) + (((size_t)b * a.Hkv + g) * a.L + (size_t)c * kChunk) * D;
+    auto r_operand = [&](int n0) {
+        const int s16 = lane % 16;
+        const bf16* src = sm.o.r + (lg * 8 + s16 / 4) * VROW + n0 + 8 * (s16 % 4);
+        const v4i16 x = lds_read_tr16(src), y = lds_read_tr16(src + 4 * VROW);
+        typedef short v8i16 __attribute__((ext_vector_type(8)));
+        const v8i16 v = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    bf16x8 bT[4];
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-        const bf16x8 aT = ld_bf16x8(sm.t + (kb * 16 + n16) * TROW + lg * 8);
+    for (int kb = 0; kb < 4; ++kb) bT[kb] = ld_bf16x8(sm.o.t + (kb * 16 + n16) * TROW + lg * 8);
 #pragma unroll
-        for (int d = 0; d < DB; ++d) {
-            const f32x4 acc = mfma16x16x32(aT, tr_operand(sm.r, VROW, 0, d * 16, lane), zero4());
+    for (int d = 0; d < D / 32; ++d) {
+        const bf16x8 r0 = r_operand(32 * d), r1 = r_operand(32 * d + 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dkb[(size_t)(kb * 16 + lg * 4 + i) * D + d * 16 + n16] = from_f32<bf16>(acc[i]);
+        for (int kb = 0; kb < 4; ++kb) {
+            const f32x4 x = mfma16x16x32(r0, bT[kb], zero4()), y = mfma16x16x32(r1, bT[kb], zero4());
+            *reinterpret_cast<uint4*>(dkb + (size_t)(kb * 16 + n16) * D + 32 * d + 8 * lg) =
+                make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]),
+                           pack_bf16x2(y[2], y[3]));
         }
     }
 }
