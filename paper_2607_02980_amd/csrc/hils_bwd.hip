@@ -37,23 +37,25 @@ __global__ void k_fill_i32(int* p, size_t n, int v) {
 // order, so the query rows it gathers stay in L2).
 // List entries are (n << 6) | slot (slot < K <= 64).
 constexpr int kInvRows = 128;
-constexpr int kInvHist = 8192;  // chunks counted in LDS; larger L falls back to global atomics
 static_assert(kInvBucketRows % kInvRows == 0, "a block of rows lies in one bucket");
+static_assert(kInvRows % 128 == 0 && kInvRows <= 32 * 16, "tiles of 16 to 128 rows do not straddle blocks");
 
 // The entries of rows n0 .. n0 + rows - 1, kPer per thread and round with their loads in
-// flight together: f(chunk, entry) for the valid ones.
+// flight together: f(chunk, entry, gap) for the valid ones; gap: the entry before it in
+// the row is not one.
 template <typename F>
 __device__ __forceinline__ void for_entries(const InvArgs& a, int bg, int n0, int rows, F&& f) {
     constexpr int kPer = 4;
     const int32_t* idx = a.idx + ((size_t)bg * a.Nrow + a.n0 + n0) * a.K;
     const int total = rows * a.K;
     for (int e0 = threadIdx.x; e0 < total; e0 += kPer * kBlock) {
-        int c[kPer], before[kPer];
+        int c[kPer], before[kPer], before2[kPer];
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
             const int e = min(e0 + t * kBlock, total - 1);
             c[t] = idx[e];
             before[t] = idx[max(e - 1, 0)];
+            before2[t] = idx[max(e - 2, 0)];
         }
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
@@ -61,8 +63,10 @@ __device__ __forceinline__ void for_entries(const InvArgs& a, int bg, int n0, in
             if (e >= total) break;
             // (as idx_entry_valid)
             const int n = n0 + e / a.K, slot = e % a.K;
-            if (c[t] >= 0 && c[t] < n_candidates(a.n0 + n, a.W) && (slot == 0 || c[t] > before[t]))
-                f(c[t], (n << 6) | slot);
+            const int nc = n_candidates(a.n0 + n, a.W);
+            if (c[t] >= 0 && c[t] < nc && (slot == 0 || c[t] > before[t]))
+                f(c[t], (n << 6) | slot,
+                  slot > 0 && !(before[t] >= 0 && before[t] < nc && (slot == 1 || before[t] > before2[t])));
         }
     }
 }
@@ -75,10 +79,43 @@ __global__ __launch_bounds__(kBlock) void k_inv_count(InvArgs a, int nR, int bro
     const int nC = a.L / kChunk, R = n0 / brows;
     const bool lds = nC <= kInvHist;
     int* gcnt = counts + (size_t)bg * nC * nR + (size_t)R * nC;
+    const int rows = min(kInvRows, a.N - n0);
+    __shared__ unsigned s_uni, s_gap;  // bit t: tile t of the block is flagged; has a row with gaps
+    if (tid == 0) s_uni = s_gap = 0u;
+    if (a.flags) {
+        // the unions of the block's tiles: their chunks' bitmaps in the histogram's place,
+        // as many tiles at once as fit
+        const int ntile = (rows + a.QT - 1) / a.QT, nw = (nC + 31) / 32, fit = min(ntile, kInvHist / nw);
+        for (int t0 = 0; t0 < ntile; t0 += fit) {
+            __syncthreads();
+            for (int i = tid; i < fit * nw; i += kBlock) s_hist[i] = 0;
+            __syncthreads();
+            for_entries(a, bg, n0, rows, [&](int c, int ent, bool gap) {
+                const int t = ((ent >> 6) - n0) / a.QT - t0;
+                if (t >= 0 && t < fit) atomicOr(&s_hist[t * nw + (c >> 5)], 1 << (c & 31));
+                if (gap && t >= 0 && t < fit) atomicOr(&s_gap, 1u << (t0 + t));
+            });
+            __syncthreads();
+            for (int t = tid / kWave; t < fit && t0 + t < ntile; t += kBlock / kWave) {
+                int u = 0;
+                for (int i = tid % kWave; i < nw; i += kWave) u += __popc((unsigned)s_hist[t * nw + i]);
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) u += __shfl_xor(u, o, kWave);
+                if (tid % kWave == 0) {
+                    const bool f = u <= a.umax && !(s_gap >> (t0 + t) & 1u);
+                    if (f) atomicOr(&s_uni, 1u << (t0 + t));
+                    a.flags[(size_t)bg * ((a.N + a.QT - 1) / a.QT) + n0 / a.QT + t0 + t] = f;
+                }
+            }
+        }
+        __syncthreads();
+    }
     if (lds)
         for (int c = tid; c < nC; c += kBlock) s_hist[c] = 0;
     __syncthreads();
-    for_entries(a, bg, n0, min(kInvRows, a.N - n0), [&](int c, int) {
+    const unsigned uni = s_uni;
+    for_entries(a, bg, n0, rows, [&](int c, int ent, bool) {
+        if (uni && (uni >> (((ent >> 6) - n0) / a.QT) & 1u)) return;
         if (lds)
             atomicAdd(&s_hist[c], 1);
         else
@@ -99,17 +136,25 @@ __global__ __launch_bounds__(kBlock) void k_inv_fill(InvArgs a, int nR, int brow
     int* gcur = cursor + (size_t)bg * nC * nR + (size_t)R * nC;
     int* lst = list + (size_t)bg * a.N * a.K;
     const int rows = min(kInvRows, a.N - n0);
+    unsigned uni = 0u;  // bit t: tile t of the block is flagged, its rows left out
+    if (a.flags)
+        for (int t = 0; t * a.QT < rows; ++t)
+            uni |= (unsigned)(a.flags[(size_t)bg * ((a.N + a.QT - 1) / a.QT) + n0 / a.QT + t] != 0) << t;
+    auto left_out = [&](int ent) { return uni && (uni >> (((ent >> 6) - n0) / a.QT) & 1u); };
     if (lds) {
         for (int c = tid; c < nC; c += kBlock) s_hist[c] = 0;
         __syncthreads();
-        for_entries(a, bg, n0, rows, [&](int c, int) { atomicAdd(&s_hist[c], 1); });
+        for_entries(a, bg, n0, rows, [&](int c, int ent, bool) {
+            if (!left_out(ent)) atomicAdd(&s_hist[c], 1);
+        });
         __syncthreads();
         // reserve this block's range of every chunk it touches; s_hist becomes the running position
         for (int c = tid; c < nC; c += kBlock)
             if (s_hist[c]) s_hist[c] = atomicAdd(&gcur[c], s_hist[c]);
         __syncthreads();
     }
-    for_entries(a, bg, n0, rows, [&](int c, int ent) {
+    for_entries(a, bg, n0, rows, [&](int c, int ent, bool) {
+        if (left_out(ent)) return;
         const int pos = lds ? atomicAdd(&s_hist[c], 1) : atomicAdd(&gcur[c], 1);
         lst[pos] = ent;
     });

@@ -92,11 +92,17 @@ void timing_end(hipStream_t s);
 // Inverse index of a selection: for every (b, g, chunk) the rows n that chose it.
 // The inverse index of rows n0 .. n0 + N - 1 of idx ([B, Hkv, Nrow, K]); list
 // entries hold the row relative to n0.
+// flags (nullable, L / 64 <= kInvHist): one byte per tile of QT rows, written: 1 if the
+// union of its rows' chunks counts at most umax and no row has an invalid entry before a
+// valid one (a given selection may); such a tile's rows are left out.
 struct InvArgs {
     const int32_t* idx;
     int B, Hkv, N, K, W, L;
     int n0, Nrow;
+    uint8_t* flags = nullptr;
+    int QT = 0, umax = 0;
 };
+constexpr int kInvHist = 8192;  // chunks counted in LDS; larger L falls back to global atomics
 struct InvLayout {
     size_t counts, offsets, cursor, list;  // byte offsets from the workspace base
     size_t boff;    // [bg][nC * nR + 1]: start of the (chunk, row bucket) sub-lists

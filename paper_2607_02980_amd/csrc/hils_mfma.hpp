@@ -218,4 +218,12 @@ __device__ __forceinline__ int xcd_remap(int physical, int n) {
     return logical;
 }
 
+// The same in runs of 4 neighbours dealt over the XCDs in turn, for blocks whose work
+// depends on where in the sequence they lie (a contiguous eighth of it per XCD would load
+// the XCDs unevenly).
+__device__ __forceinline__ int xcd_runs(int physical, int n) {
+    if (physical >= n / 32 * 32) return physical;
+    return physical / 32 * 32 + physical % 8 * 4 + physical / 8 % 4;
+}
+
 }  // namespace hils

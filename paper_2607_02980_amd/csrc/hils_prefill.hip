@@ -51,7 +51,7 @@ constexpr int kSQ = 32;   // queries per score tile (two 16-row MFMA tiles)
 constexpr int kSL = 256;  // candidate chunks per score slice
 
 struct PfLayout {
-    size_t part, wgt, inv_base;
+    size_t part, wgt, inv_base, flags;
     InvLayout inv;
     size_t total;
 };
@@ -81,7 +81,8 @@ PfLayout pf_layout(int B, int Hq, int Hkv, int N, int L, int d, int K, int row_e
     w.wgt = align256(w.part + (size_t)B * Hq * Np * K * d * sizeof(uint16_t));
     w.inv_base = align256(w.wgt + (size_t)B * Hq * Np * K * sizeof(float));
     w.inv = inv_layout(B, Hkv, N, L, K, w.inv_base, row_end);
-    w.total = w.inv.end;
+    w.flags = w.inv.end;  // one byte per tile of the local pass
+    w.total = align256(w.flags + (size_t)B * Hkv * (Np / QT));
     return w;
 }
 
@@ -768,9 +769,12 @@ struct LocalCfg {
 // no partials go through HBM.  The union is built in LDS from the rows' idx: a
 // bitmap over the chunks, then the set bits in order (dynamic LDS: the bitmap,
 // the rows' valid entries, the union list).
+// flags (nullable): the tiles marked there are left to the union kernel (the inverse index
+// leaves their rows out, see k_inv_count), the others to the records'; two launches, as
+// both paths in one kernel spill 51 registers at d = 128.
 template <int D, int G, bool UNION, bool ROUTE>
 __global__ __launch_bounds__(LocalCfg<G>::NT, 4) void k_pf_local(FwdArgs a, const bf16* part, const float* wgt, int n0,
-                                                                 int Ns) {
+                                                                 int Ns, const uint8_t* flags) {
     using C = LocalCfg<G>;
     constexpr int KS = Tiles<D>::KS, DB = Tiles<D>::DB;
     constexpr int KROW = Tiles<D>::KROW, VROW = D + 16;
@@ -782,12 +786,19 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 4) void k_pf_local(FwdArgs a, cons
     const int tid = threadIdx.x, w = wave_id(), lane = tid % kWave, lg = lane / 16;
     // the tiles of rows n0 .. n0 + Ns - 1 (the partials are indexed from n0)
     const int ntiles = (Ns + C::QT - 1) / C::QT;
-    const int tile = xcd_remap(blockIdx.x, ntiles), g = blockIdx.y, b = blockIdx.z;
+    // UNION: a 1-D grid, KV group fastest (with 8 groups each XCD stages one group's chunks
+    // from its L2), the late tiles with the largest unions first.  Records: neighbouring
+    // tiles share windows, so they go to the XCDs in runs.  (With a contiguous eighth of the
+    // tiles per XCD, the early tiles that take the union were one XCD's: 1095 us at 32K.)
+    const int rest = blockIdx.x / a.Hkv;
+    const int tile = UNION ? ntiles - 1 - rest % ntiles : xcd_runs(blockIdx.x, ntiles);
+    const int g = UNION ? blockIdx.x % a.Hkv : blockIdx.y, b = UNION ? rest / ntiles : blockIdx.z;
     const int q0 = n0 + tile * C::QT;
     const int qlast = min(q0 + C::QT - 1, a.N - 1);
     const int kbeg = n_candidates(q0, a.W) * kChunk;
     const int kfull = n_candidates(qlast, a.W) * kChunk;  // keys >= kfull are in every row's window...
     const size_t bg = (size_t)b * a.Hkv + g;
+    if (flags && (flags[bg * ntiles + tile] != 0) != UNION) return;  // the whole block
     const bf16* kbase = as<bf16>(a.k) + bg * a.L * D;
     const bf16* vbase = as<bf16>(a.v) + bg * a.L * D;
     const float c1 = a.scale * kLog2e;
@@ -1169,16 +1180,14 @@ struct PfRun {
         // Short sequences: with few more chunks than a row retrieves, a tile's union is
         // not much larger than one row's selection, and computing it beats the index, the
         // records and three launches.  Attention with i.i.d. queries (like neighbours make the
-        // union smaller), d = 128, K = 16, 32 heads, chunk-major and union: groups of 4, 2 x
-        // 2000 tokens (32 chunks) 286 and 161 us, 3001 (47) 456 and 315, 1 x 4500 (71) 384 and
-        // 339, 6500 (102) 562 and 743; groups of 8, 4500: 445 and 324, 6500: 663 and 669;
-        // K = 32, 6500: 916 and 816; K = 4, 2000 (32): 143 and 141.  Narrower groups put more
-        // queries in a wave: groups of 2 (d = 64), 3001: 150 and 117, 4500: 122 and 129;
-        // groups of 1, 2000: 110 and 76, 3001: 137 and 148.  A given selection may have gaps,
-        // which the union does not look past: it stays chunk-major.
+        // union smaller), K = 16, chunk-major and union in us: d = 128, 16 heads in groups of
+        // 1: 4500 tokens (71 chunks) 234 and 176, 6500 (102) 327 and 296, 9000 (141) 455 and
+        // 519; 16 heads in groups of 2: 210 and 169, 308 and 277, 425 and 490; K = 4, 32 heads
+        // in groups of 4, 2 x 2000 (32): 138 and 110, 2 x 3001 (47): 199 and 208.  At d = 64 the
+        // records are half as long and a union step is not: 16 heads in groups of 2, 4500:
+        // 124 and 110, 6500: 171 and 186.
         const int nC = a.L / kChunk;
-        const bool few_chunks =
-            !a.given_idx && !a.union_pack && nC <= (G == 1 ? 2 * a.K + 4 : G == 2 ? 3 * a.K + 4 : 4 * a.K + 8);
+        const bool few_chunks = !a.union_pack && nC <= (D == 128 ? 4 * a.K + 24 : 3 * a.K + 16);
         bool cleared = false;  // the inverse index's counters
         if (!a.given_idx) {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);
@@ -1221,19 +1230,34 @@ struct PfRun {
                 HILS_LAUNCH("k_pf_score", (k_pf_score<D, G, false>), grid, dim3(kSW * kWave), dyn, s, a);
             }
         }
-        const dim3 lgrid((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT, a.Hkv, a.B);
-        if (a.union_pack || few_chunks) {
+        const dim3 lgrid((unsigned)((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT) * a.Hkv * a.B);
+        const int qk = LocalCfg<G>::QT * a.K;
+        const size_t dyn = (size_t)((nC + 31) / 32 + qk + min(nC, qk)) * sizeof(int);  // the union's lists
+        if (a.union_pack || (few_chunks && !a.given_idx)) {
             // one-load-multiple-compute: no inverse index, no per-slot partials
-            const int qk = LocalCfg<G>::QT * a.K;
-            const size_t dyn = (size_t)((nC + 31) / 32 + qk + min(nC, qk)) * sizeof(int);
             if (a.q_route)
                 HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, true>), lgrid, dim3(LocalCfg<G>::NT), dyn, s, a,
-                            (const bf16*)nullptr, (const float*)nullptr, 0, a.N);
+                            (const bf16*)nullptr, (const float*)nullptr, 0, a.N, (const uint8_t*)nullptr);
             else
                 HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, false>), lgrid, dim3(LocalCfg<G>::NT), dyn, s, a,
-                            (const bf16*)nullptr, (const float*)nullptr, 0, a.N);
+                            (const bf16*)nullptr, (const float*)nullptr, 0, a.N, (const uint8_t*)nullptr);
             return hipGetLastError();
         }
+        // Otherwise, with d = 128, groups of 4 or 8 and K >= 16, each tile takes the cheaper
+        // way by the size of its union, which the index counts: the records of a tile cost 310
+        // to 410 ns at K = 16, a union chunk 7 (groups of 4) or 5 (of 8).  Early tiles have few
+        // candidates, and the queries of trained models retrieve alike.  32 heads, K = 16, all
+        // tiles chunk-major and by tile: 8000 tokens in groups of 4, i.i.d. 749 and 701 us, AR(1)
+        // queries (rho 0.97) 741 and 678; groups of 8: 848 and 767, 16000 with rho 0.97: 1756 and
+        // 1128; 32K, groups of 4: 3325 and 3177; K = 32, 8000: 1199 and 798.  Left out, because
+        // the second launch and the count cost more than the early tiles save there: K = 8
+        // (469 and 490), K = 4 (323 and 346), groups of 2 (405 and 412) and 1 (470 and 484), d =
+        // 64 (246 and 286).  (A given selection takes the same way as one made here, tile by
+        // tile, except that the union does not look past gaps in a row: such tiles stay
+        // chunk-major.)
+        const bool per_tile = nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16));
+        uint8_t* flags = per_tile ? reinterpret_cast<uint8_t*>(ws + ly.flags) : nullptr;
+        const int umax = few_chunks ? nC : G == 8 ? 4 * a.K : 5 * a.K / 2;
         const int* boff = reinterpret_cast<const int*>(ws + ly.inv.boff);
         const int* list = reinterpret_cast<const int*>(ws + ly.inv.list);
         const int4* work = reinterpret_cast<const int4*>(ws + ly.inv.work);
@@ -1241,7 +1265,7 @@ struct PfRun {
         const dim3 cgrid((unsigned)(ly.inv.max_work_bg * a.B * a.Hkv));
         for (int n0 = 0; n0 < a.N; n0 += seg) {
             const int Ns = std::min(seg, a.N - n0);
-            const InvArgs ia{a.idx, a.B, a.Hkv, Ns, a.K, a.W, a.L, n0, a.N};
+            const InvArgs ia{a.idx, a.B, a.Hkv, Ns, a.K, a.W, a.L, n0, a.N, flags, LocalCfg<G>::QT, umax};
             launch_inverse_index(ia, ly.inv, a.ws, s, true, cleared && n0 == 0);
             if (a.q_route)
                 HILS_LAUNCH("k_pf_chunks", (k_pf_chunks<D, G, true>), cgrid, dim3(kBlock), 0, s, a, boff, ly.inv.nR,
@@ -1250,8 +1274,15 @@ struct PfRun {
                 HILS_LAUNCH("k_pf_chunks", (k_pf_chunks<D, G, false>), cgrid, dim3(kBlock), 0, s, a, boff, ly.inv.nR,
                             list, work, ly.inv.max_work_bg, nwork, part, wgt, n0, Ns);
             const dim3 sgrid((Ns + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT, a.Hkv, a.B);
+            const dim3 ugrid(sgrid.x * a.Hkv * a.B);
+            if (flags && a.q_route)
+                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, true>), ugrid, dim3(LocalCfg<G>::NT), dyn, s, a,
+                            (const bf16*)nullptr, (const float*)nullptr, n0, Ns, (const uint8_t*)flags);
+            else if (flags)
+                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, false>), ugrid, dim3(LocalCfg<G>::NT), dyn, s, a,
+                            (const bf16*)nullptr, (const float*)nullptr, n0, Ns, (const uint8_t*)flags);
             HILS_LAUNCH("k_pf_local", (k_pf_local<D, G, false, false>), sgrid, dim3(LocalCfg<G>::NT), 0, s, a,
-                        (const bf16*)part, (const float*)wgt, n0, Ns);
+                        (const bf16*)part, (const float*)wgt, n0, Ns, (const uint8_t*)flags);
         }
         return hipGetLastError();
     }

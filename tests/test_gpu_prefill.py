@@ -185,13 +185,14 @@ def test_prefill_is_deterministic():
         assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1530, 2, 4, 4, 0.97), (1540, 1, 4, 4, 0.0),
-                                           (1330, 1, 8, 6, 0.0), (770, 3, 1, 4, 0.0), (833, 3, 1, 4, 0.0),
-                                           (1024, 1, 2, 4, 0.0), (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0)])
+@pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1790, 2, 4, 4, 0.97), (1800, 1, 4, 4, 0.0),
+                                           (1330, 1, 8, 6, 0.0), (770, 3, 1, 4, 0.0), (1850, 3, 1, 4, 0.0),
+                                           (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0)])
 def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
-    """Few more chunks than a row retrieves (the union path; on both sides of its limits,
-    2 K + 4, 3 K + 4 and 4 K + 8 chunks for groups of 1, 2 and more) against the chunk-major pass, which a given
-    selection always takes; and a NaN value stays with the rows that attend it."""
+    """Few more chunks than a row retrieves (the union path; on both sides of its limit,
+    3 K + 16 chunks at d = 64) against the same
+    selection given with a gap before it, which always takes the chunk-major pass, and
+    without one, which takes the same path; and a NaN value stays with the rows that attend it."""
     from paper_2607_02980_amd import hils
 
     p = hils.Params(B=2, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=64, topk=K, window=130)
@@ -205,9 +206,15 @@ def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
         return hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"], dev["q_route"], idx=idx)
 
     out, lse, idx = run(0)
-    ref, rlse, _ = run(hils.HILS_FLAG_GIVEN_IDX, idx.clone())
-    # the chunk-major records round each chunk's output to bf16 (2^-9), the union does not
-    assert (out.float() - ref.float()).abs().max() <= 2e-2 and (lse - rlse).abs().max() <= 2e-4
+    same, slse, _ = run(hils.HILS_FLAG_GIVEN_IDX, idx.clone())
+    assert torch.equal(out, same) and torch.equal(lse, slse)
+    if K < 64:
+        p.topk = K + 1
+        gap = torch.cat([torch.full_like(idx[..., :1], -1), idx], -1).contiguous()
+        ref, rlse, _ = run(hils.HILS_FLAG_GIVEN_IDX, gap)
+        p.topk = K
+        # the chunk-major records round each chunk's output to bf16 (2^-9), the union does not
+        assert (out.float() - ref.float()).abs().max() <= 2e-2 and (lse - rlse).abs().max() <= 2e-4
     j = 200  # in chunk 3
     dev["v"][0, 0, j] = float("nan")
     n = torch.arange(N, device="cuda")
@@ -218,3 +225,27 @@ def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
     assert torch.equal(idx, idx2)
     far = ~sees & ~near
     assert torch.equal(out2[0, :G, far], out[0, :G, far]) and torch.isnan(out2[0, :G, sees]).all()
+
+
+@pytest.mark.parametrize("N,Hkv,G,K,d", [(6200, 2, 4, 16, 128), (5700, 1, 8, 17, 128), (6000, 1, 4, 20, 128),
+                                         (4100, 2, 1, 16, 64)])
+def test_tiles_of_both_kinds(N, Hkv, G, K, d):
+    """Sequences whose early tiles take the union and whose later ones the chunk-major pass
+    (adjacent queries alike in the second half, so that some later ones take it too): every
+    row against the oracle, and bitwise the same when given the selection."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=1, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=d, topk=K, window=200)
+    host = host_inputs(p, 372, bias=True)
+    alike = synth.ar1_host(host["q"].shape, 373, "bf16", 0.999)
+    host["q"][:, :, N // 2:] = alike[:, :, N // 2:]
+    dev = to_device(host, p)
+    out, lse, idx = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"])
+    p.flags = hils.HILS_FLAG_GIVEN_IDX
+    same, slse, _ = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"], idx=idx.clone())
+    assert torch.equal(out, same) and torch.equal(lse, slse)
+    p.flags = 0
+    args = (oshape(p), *(np32(host[n]) for n in ("q", "k", "v", "lmk")))
+    ref = oracle.fwd(*args, bias=np32(host["bias"]), idx=idx.cpu().numpy())
+    check_close("out", np32(out), ref["out"], "bf16")
+    check_lse(np32(lse), ref["lse"], "bf16")
