@@ -324,7 +324,9 @@ __global__ __launch_bounds__(8 * kWave) void k_pf_lse(FwdArgs a) {
     __shared__ __align__(16) bf16 s_l[2][st_size<D>(kLseCand)];
     __shared__ float s_b[2][kLseCand];
     const int tid = threadIdx.x, w = wave_id(), lane = tid % kWave, lg = lane / 16;
-    const int q0 = blockIdx.x * kLseRows, h = blockIdx.y, b = blockIdx.z;
+    const int ntiles = (a.N + kLseRows - 1) / kLseRows;
+    const int h = blockIdx.x % a.Hq, rest = blockIdx.x / a.Hq, b = rest / ntiles;
+    const int q0 = (ntiles - 1 - rest % ntiles) * kLseRows;
     const int G = a.Hq / a.Hkv, hl = (a.Hl == a.Hq) ? h : h / G;
     const int nC = a.L / kChunk;
     const int qlast = min(q0 + kLseRows - 1, a.N - 1);
@@ -434,6 +436,11 @@ __global__ __launch_bounds__(8 * kWave) void k_pf_lse(FwdArgs a) {
 // the records' area of the workspace, which the chunk pass fills only after the
 // selection.  NORM (per-head normalised ranking): each head's scores less the
 // (row, head) log-sum-exp that k_pf_lse left in lse, before the max over heads.
+// 1-D grid here and in k_pf_lse: KV group (head) fastest, so that with 8 groups an XCD's
+// L2 serves one group's landmarks, and the late tiles, with the most candidates, first
+// (tiles fastest and ascending: 68 against 52 us at 12K tokens, 4 groups of 8 heads).
+// Two row tiles per wave, each landmark operand feeding two products (234 VGPRs, 4 waves),
+// took 384 us at 32K, groups of 4, against 229.
 template <int D, int G, bool NORM>
 __global__ __launch_bounds__(8 * kWave) void k_pf_sigma(FwdArgs a, float* sig) {
     constexpr int KS = D / 32, NT = 8 * kWave;
@@ -442,7 +449,9 @@ __global__ __launch_bounds__(8 * kWave) void k_pf_sigma(FwdArgs a, float* sig) {
     __shared__ __align__(16) bf16 s_l[2][st_size<D>(kLseCand)];
     __shared__ float s_b[2][kLseCand];
     const int tid = threadIdx.x, w = wave_id(), lane = tid % kWave, lg = lane / 16;
-    const int q0 = blockIdx.x * kLseRows, g = blockIdx.y, b = blockIdx.z;
+    const int ntiles = (a.N + kLseRows - 1) / kLseRows;
+    const int g = blockIdx.x % a.Hkv, rest = blockIdx.x / a.Hkv, b = rest / ntiles;
+    const int q0 = (ntiles - 1 - rest % ntiles) * kLseRows;
     const int nC = a.L / kChunk;
     const int qlast = min(q0 + kLseRows - 1, a.N - 1);
     const int nct = min(nC, n_candidates(qlast, a.W));
@@ -1193,14 +1202,14 @@ struct PfRun {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);
             const size_t dyn = score_dyn_lds(a.K);
             if (a.head_norm) {
-                const dim3 lgr((unsigned)((a.N + kLseRows - 1) / kLseRows), a.Hq, a.B);
+                const dim3 lgr((unsigned)((a.N + kLseRows - 1) / kLseRows) * a.Hq * a.B);
                 HILS_LAUNCH("k_pf_lse", k_pf_lse<D>, lgr, dim3(8 * kWave), 0, s, a);
             }
             if (nC <= 16 * kWave && !a.union_pack &&
                 (size_t)a.B * a.Hkv * a.N * nC * sizeof(float) <= ly.wgt - ly.part) {
                 // the split scorer: sigma in the records' area (see k_pf_sigma)
                 float* sigma = reinterpret_cast<float*>(ws + ly.part);
-                const dim3 sgr((unsigned)((a.N + kLseRows - 1) / kLseRows), a.Hkv, a.B);
+                const dim3 sgr((unsigned)((a.N + kLseRows - 1) / kLseRows) * a.Hkv * a.B);
                 if (a.head_norm)
                     HILS_LAUNCH("k_pf_sigma", (k_pf_sigma<D, G, true>), sgr, dim3(8 * kWave), 0, s, a, sigma);
                 else
