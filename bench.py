@@ -80,7 +80,8 @@ def prefill_kernel_model(B, Hq, Hkv, N, L, d, S, K, W, elem=2):
     k_pf_chunks: per selected (row, head, chunk) QK^T + PV over S keys (4dS) and
                  the surrogate score (2d); reads q and the K/V once.
     k_pf_local : window QK^T + PV, 4d per (row, head, window key), and the fusion;
-                 reads q and K/V once, writes out and lse.
+                 reads q and K/V once, writes out and lse.  (The tiles with small
+                 unions do both in k_pf_union: main() moves their share there.)
     design_bytes: the records k_pf_chunks writes and k_pf_local reads back (the bf16
                  chunk output and the fp32 score per (row, head, slot)).
     """
@@ -201,6 +202,19 @@ def chunk_overlap(idx, M=16):
     return float(vals.mean()) if vals.size else float("nan")
 
 
+def union_share(idx, G, most):
+    """The tiles of 128 / G rows whose union counts at most `most` chunks, which the prefill
+    computes in k_pf_union instead of the chunk-major pass: (share of the tiles, share of
+    the retrieved (row, chunk) pairs in them).  32K at groups of 4: most = 5 K / 2."""
+    B, Hkv, N, K = idx.shape
+    QT = 128 // G
+    blk = np.sort(idx[:, :, :N // QT * QT].reshape(-1, QT * K), axis=-1)
+    uniq = (np.diff(blk, axis=-1, prepend=-1) != 0).sum(axis=-1)
+    small = uniq <= most
+    pairs = (blk >= 0).sum(axis=-1)
+    return float(small.mean()), float(pairs[small].sum() / max(1, pairs.sum()))
+
+
 def bench_prefill(torch, hils, synth, W_, steps, warmup, flags=0, rho=None):
     """Times `steps` prefill calls (HIP events on the library's stream, no
     per-kernel events), then a second pass with per-kernel timing for the
@@ -235,6 +249,7 @@ def bench_prefill(torch, hils, synth, W_, steps, warmup, flags=0, rho=None):
     for k in kernels.values():
         k["avg_ms"] = k["total_ms"] / max(1, k["launches"])
     p.overlap16 = chunk_overlap(idx.cpu().numpy(), 16) if p.topk <= 64 and p.dtype == "bf16" else float("nan")
+    p.union_share = union_share(idx.cpu().numpy(), p.Hq // p.Hkv, 5 * p.topk // 2) if p.dtype == "bf16" else (0.0, 0.0)
     p.ms_mean = ms_mean
     del dev, ws
     torch.cuda.empty_cache()
@@ -477,6 +492,12 @@ def main():
         return
     p, host, ms, kernels = bench_prefill(torch, hils, synth, Wp, args.steps, args.warmup)
     model = prefill_kernel_model(p.B, p.Hq, p.Hkv, p.N, p.L, p.d, p.chunk, p.topk, p.window)
+    # the tiles with small unions leave the chunk-major pass: their share of the work
+    tiles, pairs = p.union_share
+    chunk, local = model["k_pf_chunks"], model["k_pf_local"]
+    model["k_pf_union"] = {"flop": pairs * chunk["flop"] + tiles * local["flop"], "bytes": tiles * local["bytes"]}
+    chunk.update(flop=(1 - pairs) * chunk["flop"], design_bytes=(1 - pairs) * chunk["design_bytes"])
+    local.update(flop=(1 - tiles) * local["flop"], design_bytes=chunk["design_bytes"])
     table = {}
     for name, k in kernels.items():
         row = {"avg_ms": round(k["avg_ms"], 4), "launches": k["launches"]}
@@ -518,6 +539,7 @@ def main():
                      "kernel_avg_ms": d["avg_ms"]},
         "extra": {"ms_per_step_mean": round(p.ms_mean, 4),
                   "prefill_kernels": table,
+                  "prefill_union_share": {"tiles": round(tiles, 4), "retrieved_pairs": round(pairs, 4)},
                   "prefill_useful_mfma_frac": round((attn_flops + score_flops) / (ms * 1e-3) / 1e12
                                                     / BF16_MFMA_PEAK_TFLOPS, 5),
                   "prefill_method_bytes": mbytes,

@@ -94,12 +94,13 @@ typedef enum {
  * the kept candidates.  Ignored by hils_bwd (the selection is given). */
 #define HILS_FLAG_HEAD_NORM_SELECT 4u
 
-/* Prefill flag (bf16): compute the retrieved-chunk terms by union packing, the
- * one-load-multiple-compute scheme of Sec. 4.2 — each tile of adjacent queries
+/* Prefill flag (bf16): compute the retrieved-chunk terms of every tile by union packing,
+ * the one-load-multiple-compute scheme of Sec. 4.2 — each tile of adjacent queries
  * loads the union of their selected chunks once and computes every chunk for
- * all of its rows (rows that did not select a chunk get weight 0).  Same
- * results as the default chunk-major pass; faster when adjacent queries select
- * overlapping chunks (as trained models do), slower when they do not.  Needs no
+ * all of its rows (rows that did not select a chunk get weight 0).  Without the flag the
+ * library takes this way where the tiles' unions are small (short sequences, early
+ * tiles, queries that retrieve alike) and the chunk-major pass elsewhere, so the flag is
+ * rarely faster.  Same results up to the rounding of the chunk-major records.  Needs no
  * workspace (hils_workspace_size reports 0 under this flag).  Ignored by the
  * fp32 path, decode and the backward. */
 #define HILS_FLAG_UNION_PACKING 8u

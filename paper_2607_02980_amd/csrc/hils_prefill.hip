@@ -8,7 +8,10 @@
 //                    than 1024 candidate chunks, when that array does not fit the
 //                    records' area and under union packing, k_pf_score does both
 //                    in one pass per 32-query tile.
-//   inverse index    rows that selected each (b, g, chunk)
+//   inverse index    rows that selected each (b, g, chunk); tiles whose rows share few
+//                    chunks are left out and go to k_pf_union (k_pf_local<.., UNION>),
+//                    which computes the union of a tile's chunks for all its rows and
+//                    needs no records; short sequences go there whole
 //   P3 k_pf_chunks   chunk-major: K_c, V_c staged once in LDS, the selecting rows
 //                    gathered 16 at a time; S^T = K_c Q^T, the intra-chunk softmax
 //                    (Eq. (10)) and s^ of the (row, head, chunk).  Each (row, head,

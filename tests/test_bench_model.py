@@ -9,6 +9,8 @@ the keys from chunk |C_i| on up to i."""
 import subprocess
 import sys
 
+import numpy as np
+
 import bench
 
 
@@ -37,6 +39,19 @@ def test_prefill_model_matches_row_sums():
     assert abs(m["k_pf_chunks"]["flop"] / 1e9 - 536.2) < 0.1
     attn, score = bench.prefill_work(B, Hq, Hkv, N, d, S, K, W)
     assert attn == B * Hq * 4 * d * (win + S * sel) and score == B * Hq * 2 * d * cand
+
+
+def test_union_share_counts_tiles_and_pairs():
+    # two tiles of 32 rows (groups of 4), 3 slots: the first's rows retrieve chunks {0, 1}
+    # (one slot empty), the second's 32 different pairs and chunk 9
+    idx = np.full((1, 1, 64, 3), -1, np.int32)
+    idx[0, 0, :32, :2] = [0, 1]
+    idx[0, 0, 32:, 0] = 9
+    idx[0, 0, 32:, 1] = 10 + np.arange(32)
+    idx[0, 0, 32:, 2] = 50 + np.arange(32)
+    assert bench.union_share(idx, 4, 1) == (0.0, 0.0)
+    assert bench.union_share(idx, 4, 2) == (0.5, 64 / (64 + 96))
+    assert bench.union_share(idx, 4, 65) == (1.0, 1.0)
 
 
 def test_decode_bytes_match_the_step():
