@@ -1232,8 +1232,8 @@ __device__ void fuse_row(const FwdArgs& a, const DecLayout& ly, FuseSmem<G>& fs,
             for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], o, kWave);
         const size_t row = q_row(a, b, g * G + hh, n);
         if (sub == 0)
-            *reinterpret_cast<uint2*>(as_mut<bf16>(a.out) + row * D + d0) =
-                make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+            store_unaligned(as_mut<bf16>(a.out) + row * D + d0,
+                make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])));
         if (lane == 0) a.lse[row] = L;
     }
 }
@@ -1727,8 +1727,8 @@ __device__ void mq_fuse(const FwdArgs& a, const R& recs, int U, const unsigned* 
                 if (wt[j] != 0.f) acc += wt[j] * v[j];
         }
         const size_t orow = q_row(a, b, g * G + r % G, n0 + q);
-        *reinterpret_cast<uint2*>(as_mut<bf16>(a.out) + orow * D + d0) =
-            make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+        store_unaligned(as_mut<bf16>(a.out) + orow * D + d0,
+            make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])));
         if (d0 == 0) a.lse[orow] = s_lse[r];
     }
 }

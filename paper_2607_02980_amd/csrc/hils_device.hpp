@@ -64,6 +64,13 @@ __device__ __forceinline__ void load8(const float* p, float* o) {
     o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
 }
 
+// 8- and 16-byte stores to a caller's array, of which only the alignment of its elements
+// is known (a view into a larger one); global memory takes them in one instruction.
+template <typename V>
+__device__ __forceinline__ void store_unaligned(bf16* p, const V& x) {
+    __builtin_memcpy(p, &x, sizeof(V));
+}
+
 // ---- wave reductions (all 64 lanes receive the result) --------------------
 
 __device__ __forceinline__ float wave_sum(float x) {

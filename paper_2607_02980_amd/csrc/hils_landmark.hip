@@ -439,9 +439,9 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
             const f32x4 x = mfma16x16x32(r0, bT[kb], zero4()), y = mfma16x16x32(r1, bT[kb], zero4());
-            *reinterpret_cast<uint4*>(dkb + (size_t)(kb * 16 + n16) * D + 32 * d + 8 * lg) =
-                make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]),
-                           pack_bf16x2(y[2], y[3]));
+            store_unaligned(dkb + (size_t)(kb * 16 + n16) * D + 32 * d + 8 * lg,
+                            make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]),
+                                       pack_bf16x2(y[2], y[3])));
         }
     }
 }

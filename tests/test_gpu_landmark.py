@@ -95,3 +95,34 @@ def test_landmark_is_deterministic():
     torch.cuda.synchronize()
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_outputs_aligned_to_their_elements_only(d):
+    """Outputs that begin one element into a larger array get the same bits, and nothing
+    around them is written (the kernels store 8 and 16 bytes at a time)."""
+    from paper_2607_02980_amd import hils
+
+    def inner(shape):
+        n = int(np.prod(shape))
+        return torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")[1:1 + n].view(shape)
+
+    def same(x, ref):
+        base = x._base
+        assert torch.equal(x, ref)
+        assert bool((base[:1] == 7).all()) and bool((base[1 + x.numel():] == 7).all())
+
+    p = hils.Params(B=2, Hq=8, Hkv=2, N=1, L=512, d=d, topk=3, window=64)
+    log(f"[landmark] outputs one element into their arrays, d={d}")
+    lq, k, dl, db = inputs(p, 407)
+    dk = inner(k.shape)
+    ref = hils.hils_landmark_bwd(p, lq, k, dl, db)
+    hils.hils_landmark_bwd(p, lq, k, dl, db, dk=dk)
+    torch.cuda.synchronize()
+    same(dk, ref[1])
+    q = lq[:, :, :1].contiguous()
+    out = inner(q.shape)
+    ref = hils.hils_decode_fwd(p, q, k, k, dl)
+    hils.hils_decode_fwd(p, q, k, k, dl, out=out)
+    torch.cuda.synchronize()
+    same(out, ref[0])
