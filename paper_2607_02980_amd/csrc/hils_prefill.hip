@@ -1199,7 +1199,16 @@ struct PfRun {
         // records are half as long and a union step is not: 16 heads in groups of 2, 4500:
         // 124 and 110, 6500: 171 and 186.
         const int nC = a.L / kChunk;
-        const bool few_chunks = !a.union_pack && nC <= (D == 128 ? 4 * a.K + 24 : 3 * a.K + 16);
+        // With no more tiles than the chip takes at once (two per CU) a union is one chain of
+        // barriers, 2.2 us per chunk at d = 128 and 1.6 at 64 however few the tiles, and the
+        // chunk-major pass spreads over the chunks: one sequence, union and chunk-major in us:
+        // 26 chunks, K = 16, 8 heads: 71 and 95; 38, K = 4, groups of 1, 2 and 4 (8, 16 and 4
+        // heads): 96 and 72, 96 and 86, 91 and 78; 83, K = 16, 8 and 4 heads: 210 and 179,
+        // 190 and 125 (16 heads, 662 tiles: 236 and 285).
+        const bool one_round = (size_t)a.B * a.Hkv * ((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT) <=
+                               2 * (size_t)device_cus();
+        const int few = D == 128 ? 4 * a.K + 24 : 3 * a.K + 16;
+        const bool few_chunks = !a.union_pack && nC <= (one_round ? std::min(few, a.K + 24) : few);
         bool cleared = false;  // the inverse index's counters
         if (!a.given_idx) {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);
@@ -1255,7 +1264,7 @@ struct PfRun {
                             (const bf16*)nullptr, (const float*)nullptr, 0, a.N, (const uint8_t*)nullptr);
             return hipGetLastError();
         }
-        // Otherwise, with d = 128, groups of 4 or 8 and K >= 16, each tile takes the cheaper
+        // Otherwise, with d = 128, groups of 4 or 8, K >= 16 and more tiles than one round, each tile takes the cheaper
         // way by the size of its union, which the index counts: the records of a tile cost 310
         // to 410 ns at K = 16, a union chunk 7 (groups of 4) or 5 (of 8).  Early tiles have few
         // candidates, and the queries of trained models retrieve alike.  32 heads, K = 16, all
@@ -1267,7 +1276,7 @@ struct PfRun {
         // 64 (246 and 286).  (A given selection takes the same way as one made here, tile by
         // tile, except that the union does not look past gaps in a row: such tiles stay
         // chunk-major.)
-        const bool per_tile = nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16));
+        const bool per_tile = nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16 && !one_round));
         uint8_t* flags = per_tile ? reinterpret_cast<uint8_t*>(ws + ly.flags) : nullptr;
         const int umax = few_chunks ? nC : G == 8 ? 4 * a.K : 5 * a.K / 2;
         const int* boff = reinterpret_cast<const int*>(ws + ly.inv.boff);
