@@ -187,10 +187,12 @@ def test_prefill_is_deterministic():
 
 @pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1790, 2, 4, 4, 0.97), (1800, 1, 4, 4, 0.0),
                                            (1330, 1, 8, 6, 0.0), (770, 3, 1, 4, 0.0), (1850, 3, 1, 4, 0.0),
-                                           (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0)])
+                                           (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0),
+                                           (2040, 1, 4, 8, 0.0), (2100, 1, 4, 8, 0.0),   # one round: 32 and 33 chunks
+                                           (2550, 4, 4, 8, 0.0), (2610, 4, 4, 8, 0.0)])  # more tiles: 40 and 41
 def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
     """Few more chunks than a row retrieves (the union path; on both sides of its limit,
-    3 K + 16 chunks at d = 64) against the same
+    3 K + 16 chunks at d = 64, K + 24 while the tiles fit the chip at once) against the same
     selection given with a gap before it, which always takes the chunk-major pass, and
     without one, which takes the same path; and a NaN value stays with the rows that attend it."""
     from paper_2607_02980_amd import hils
@@ -228,7 +230,9 @@ def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
 
 
 @pytest.mark.parametrize("N,Hkv,G,K,d", [(6200, 2, 4, 16, 128), (5700, 1, 8, 17, 128), (6000, 1, 4, 20, 128),
-                                         (4100, 2, 1, 16, 64)])
+                                         (4100, 2, 1, 16, 64),
+                                         # more tiles than two per CU, where the two kinds mix
+                                         (5700, 3, 4, 16, 128), (6000, 2, 8, 17, 128)])
 def test_tiles_of_both_kinds(N, Hkv, G, K, d):
     """Sequences whose early tiles take the union and whose later ones the chunk-major pass
     (adjacent queries alike in the second half, so that some later ones take it too): every
