@@ -369,21 +369,9 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
     // dq' = scale K^T DS^T
     f32x4 o[DB];
     lmk_kt_times<D>(sm.k, ds, o);
-    if (hv) {
-        if (a.shared) {
-            float* dst = a.ws + row * D;
-#pragma unroll
-            for (int d = 0; d < DB; ++d) *reinterpret_cast<f32x4*>(dst + d * 16 + lg * 4) = o[d] * a.scale;
-        } else {
-            bf16* dst = as_mut<bf16>(a.dlq) + row * D;
-#pragma unroll
-            for (int d = 0; d < DB; ++d)
-                *reinterpret_cast<uint2*>(dst + d * 16 + lg * 4) = make_uint2(
-                    pack_bf16x2(a.scale * o[d][0], a.scale * o[d][1]), pack_bf16x2(a.scale * o[d][2], a.scale * o[d][3]));
-        }
-    }
     // K's tile is read; rows of the dK product into it: dk' of head m in rows m and 8 + m,
-    // q' in 16 + m and 24 + m (zero for m >= nlh), again from L2
+    // q' in 16 + m and 24 + m (zero for m >= nlh), again from L2, and before dq' is stored,
+    // which may take the place of either
     uint4 rv[32 * D / 8 / kWave];
 #pragma unroll
     for (int u = 0; u < 32 * D / 8 / kWave; ++u) {
@@ -400,6 +388,19 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
     for (int u = 0; u < 32 * D / 8 / kWave; ++u) {
         const int e = lane + u * kWave;
         *reinterpret_cast<uint4*>(sm.o.r + e / (D / 8) * VROW + (e % (D / 8)) * 8) = rv[u];
+    }
+    if (hv) {
+        if (a.shared) {
+            float* dst = a.ws + row * D;
+#pragma unroll
+            for (int d = 0; d < DB; ++d) *reinterpret_cast<f32x4*>(dst + d * 16 + lg * 4) = o[d] * a.scale;
+        } else {
+            bf16* dst = as_mut<bf16>(a.dlq) + row * D;
+#pragma unroll
+            for (int d = 0; d < DB; ++d)
+                *reinterpret_cast<uint2*>(dst + d * 16 + lg * 4) = make_uint2(
+                    pack_bf16x2(a.scale * o[d][0], a.scale * o[d][1]), pack_bf16x2(a.scale * o[d][2], a.scale * o[d][3]));
+        }
     }
     // T[key][..]: p hi, p lo, scale ds hi, scale ds lo of head n16 (lanes n16 < 8)
     if (n16 < 8) {

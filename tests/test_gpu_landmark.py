@@ -126,3 +126,20 @@ def test_outputs_aligned_to_their_elements_only(d):
     hils.hils_decode_fwd(p, q, k, k, dl, out=out)
     torch.cuda.synchronize()
     same(out, ref[0])
+
+
+@pytest.mark.parametrize("over", ["lq", "dlmk"])
+@pytest.mark.parametrize("Hq,d,dtype", [(8, 128, "bf16"), (2, 64, "bf16"), (8, 64, "f32")])
+def test_landmark_backward_in_place(over, Hq, d, dtype):
+    """dq' in the place of q' or of dk', and dk in the place of k: the bits of separate outputs
+    (a workgroup reads all it needs of a chunk before it stores any of the chunk's results)."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=2, Hq=Hq, Hkv=2, N=1, L=512, d=d, topk=1, window=1, dtype=dtype)
+    log(f"[landmark] in place: dlq over {over}, Hq={Hq} d={d} {dtype}")
+    lq, k, dl, db = inputs(p, 408)
+    dlq, dk = hils.hils_landmark_bwd(p, lq, k, dl, db)
+    dlq2, dk2 = hils.hils_landmark_bwd(p, lq, k, dl, db, dlq=lq if over == "lq" else dl, dk=k)
+    torch.cuda.synchronize()
+    same = torch.equal(dlq2, dlq), torch.equal(dk2, dk)
+    assert same == (True, True)
