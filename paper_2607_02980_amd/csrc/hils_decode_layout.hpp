@@ -1,6 +1,8 @@
 // Layout of the decode workspace, shared by the kernels and the host.
 #pragma once
 
+#include <algorithm>
+
 #include "../../include/hils.h"
 #include "hils_device.hpp"
 #include "hils_internal.hpp"
@@ -58,6 +60,14 @@ inline DecLayout dec_layout(int B, int N, int Hkv, int G, int d, int L, int K, i
     o.mq = o.lse + (HN ? (bg * o.nslices * G * 2 * 4 + 255) & ~(size_t)255 : 0);
     o.hn = o.mq + mq;
     o.total = o.hn + (HN ? ((bg * o.nslices * o.hn_words * 4 + 255) & ~(size_t)255) : 0);
+    // The size never falls as B, N or L grow, so that a workspace of the largest call serves
+    // every smaller one, whichever slices it takes: room for the survivors of 64-chunk slices
+    // up to 4 * kWave per row (the limit above) where that stays within the fixed array, and
+    // never less than the slices of 256 need.
+    const size_t most = std::min<size_t>((size_t)((o.nC + 63) / 64) * K, 4 * kWave);
+    const size_t coarse = cand(kSlice) + parts + mq;
+    const size_t fine = std::max(cand(kSlice), (bg * most * 8 + 255) & ~(size_t)255) + parts + mq;
+    o.total = std::max({o.total, coarse, std::min<size_t>(fine, HILS_DECODE_NOALLOC_SCRATCH_BYTES)});
     return o;
 }
 

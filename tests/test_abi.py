@@ -288,3 +288,32 @@ def test_prefill_record_cap_bounds_the_workspace(hils):
     # the default keeps the 512K-token prefill's workspace far below its 69 GB of records
     p512 = params(hils, B=1, Hq=32, Hkv=8, N=524288, L=524288, d=128, topk=16, window=512)
     assert hils.hils_workspace_size(p512, hils.HILS_OP_PREFILL) < 20e9 < 524288 * per_row
+
+
+def test_decode_workspace_never_shrinks_with_the_call(hils):
+    # one workspace of the longest cache and the largest batch serves every smaller call, with
+    # and without the normalised ranking; and whatever fits the fixed array goes on fitting
+    grid = [(kv, g, d, k, w) for kv, g in ((8, 4), (1, 1), (8, 1), (4, 8), (2, 2))
+            for d, k, w in ((128, 16, 512), (64, 1, 1), (128, 64, 512), (64, 4, 2000))]
+    for kv, g, d, k, w in grid:
+        def size(B, N, L, flags=0):
+            return hils.hils_workspace_size(hils.Params(B=B, Hq=kv * g, Hkv=kv, N=N, L=L, d=d, topk=k, window=w,
+                                                        flags=flags), hils.HILS_OP_DECODE)
+
+        chunks = [*range(1, 70), *range(70, 2200, 61), 4096, 4097, 16384]
+        for B, N in ((1, 1), (8, 1), (31, 1), (1, 4), (8, 2)):
+            sizes = [size(B, N, 64 * c) for c in chunks]
+            assert sizes == sorted(sizes), (kv, g, d, k, w, B, N)
+            assert all(size(B, N, 64 * c, hils.HILS_FLAG_HEAD_NORM_SELECT) >= x for c, x in zip(chunks, sizes))
+        for L in (4096, 65536, 65600, 100032, 1 << 20):
+            for N in (1, 4):
+                sizes = [size(B, N, L) for B in range(1, 130)]
+                assert sizes == sorted(sizes), (kv, g, d, k, w, L, N)
+            sizes = [size(3, N, L) for N in range(1, 40)]
+            assert sizes == sorted(sizes), (kv, g, d, k, w, L)
+        # the records and the survivors of 256-chunk slices, which every call needs at least
+        nloc = (w + 62) // 64 + 1
+        for B, L in ((1, 1 << 20), (15, 65536), (60, 32768), (112, 16384), (1300, 65536)):
+            rows, al = B * kv, lambda x: (x + 255) & ~255
+            least = al(rows * -(-L // 16384) * k * 8) + al(rows * (k + nloc) * g * (4 + d) * 4)
+            assert least <= size(B, 1, L) <= max(least, hils.HILS_DECODE_NOALLOC_SCRATCH_BYTES), (kv, g, d, k, w, B, L)
