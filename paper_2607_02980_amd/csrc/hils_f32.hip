@@ -806,10 +806,11 @@ __global__ __launch_bounds__(kThreads) void k_bwd_sum_f32(BwdArgs a, const float
 // Blocks per chunk of the key-major pass: enough for two blocks on each of the 256 CUs,
 // but no more than give every wave a tile of the window's rows, and at most 16 (the sums
 // of a block take 64 x 2 d floats).
-int key_splits(int B, int Hkv, int G, int N, int L, int W) {
-    const size_t chunks = (size_t)B * Hkv * (L / kChunk);
+int key_splits_most(int G, int N, int W) {
     const int rows = (int)std::min<long>(N, (long)kChunk + W);
-    const int most = std::max(1, std::min(16, rows * G / (kCols * kW)));
+    return std::max(1, std::min(16, rows * G / (kCols * kW)));
+}
+int key_splits(size_t chunks, int most) {
     return (int)std::min<size_t>(most, std::max<size_t>(1, 512 / chunks));
 }
 
@@ -822,12 +823,17 @@ struct F32Layout {
 F32Layout f32_layout(int B, int Hq, int Hkv, int N, int L, int d, int K, int W) {
     F32Layout w;
     const int G = Hq / Hkv;
-    w.nsplit = key_splits(B, Hkv, G, N, L, W);
+    const size_t chunks = (size_t)B * Hkv * (L / kChunk);
+    const int most = key_splits_most(G, N, W);
+    w.nsplit = key_splits(chunks, most);
+    // (chunks * nsplit blocks at most, and a bound that never falls as the call grows: a
+    // workspace of the largest call serves every smaller one)
+    const size_t blocks = std::max(chunks, std::min<size_t>(512, chunks * most));
     w.u = 0;
     w.sorted = align256(w.u + (size_t)B * Hq * N * sizeof(float));
     w.sums = align256(w.sorted + (size_t)B * Hkv * N * K * sizeof(int));
     const size_t n = ((size_t)(2 * kChunk + G) * d + G + 3) / 4 * 4;
-    w.inv_base = align256(w.sums + (size_t)B * Hkv * (L / kChunk) * w.nsplit * n * sizeof(float));
+    w.inv_base = align256(w.sums + blocks * n * sizeof(float));
     w.inv = inv_layout(B, Hkv, N, L, K, w.inv_base);
     w.total = w.inv.end;
     return w;

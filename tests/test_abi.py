@@ -317,3 +317,21 @@ def test_decode_workspace_never_shrinks_with_the_call(hils):
             rows, al = B * kv, lambda x: (x + 255) & ~255
             least = al(rows * -(-L // 16384) * k * 8) + al(rows * (k + nloc) * g * (4 + d) * 4)
             assert least <= size(B, 1, L) <= max(least, hils.HILS_DECODE_NOALLOC_SCRATCH_BYTES), (kv, g, d, k, w, B, L)
+
+
+@pytest.mark.parametrize("kv,g,d,k,w", [(1, 4, 64, 4, 512), (4, 1, 128, 64, 1), (2, 8, 128, 16, 100), (3, 2, 64, 7, 1000)])
+def test_f32_backward_workspace_never_shrinks_with_the_call(hils, kv, g, d, k, w):
+    # (up to 2048 rows, one bucket of the inverse index)
+    def size(B, N, L):
+        return hils.hils_workspace_size(hils.Params(B=B, Hq=kv * g, Hkv=kv, N=N, L=L, d=d, topk=k, window=w,
+                                                    dtype="f32"), hils.HILS_OP_BWD)
+
+    for N in (1, 60, 700, 2048):
+        first = -(-N // 64)
+        for B in (1, 3, 17):
+            sizes = [size(B, N, 64 * c) for c in range(first, first + 600)]
+            assert sizes == sorted(sizes), (N, B)
+        sizes = [size(B, N, 64 * first) for B in range(1, 600)]
+        assert sizes == sorted(sizes), N
+    sizes = [size(2, N, 2048) for N in range(1, 2049, 7)]
+    assert sizes == sorted(sizes)
