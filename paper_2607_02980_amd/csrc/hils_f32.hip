@@ -69,13 +69,20 @@ __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int
     for (int e0 = 0; e0 < nq * K; e0 += NW * kWave) {
         const int e = e0 + tid;
         const int c = e < nq * K ? tp.sel[e] : -1;
+        // the m-th time that a query names the chunk (a given row out of order may name it more
+        // than once): used by the queries that name it as often, listed by the first of them
+        const int q = e / K;
         unsigned users = 0;
         if (c >= 0) {
-            for (int t = 0; t < nq * K; ++t)
-                if (tp.sel[t] == c) users |= 1u << (t / K);
+            int m = 1;
+            for (int t = q * K; t < e; ++t) m += tp.sel[t] == c;
+            for (int i = 0; i < nq; ++i) {
+                int times = 0;
+                for (int t = i * K; t < (i + 1) * K; ++t) times += tp.sel[t] == c;
+                users |= (unsigned)(times >= m) << i;
+            }
         }
-        // the first of its queries lists it
-        const bool lead = c >= 0 && (users & ((1u << (e / K)) - 1u)) == 0;
+        const bool lead = c >= 0 && (users & ((1u << q) - 1u)) == 0;
         const uint64_t bal = __ballot(lead);
         if (lane == 0) tp.wave_n[w] = popc64(bal);
         __syncthreads();

@@ -103,3 +103,27 @@ def test_f32_values_stay_with_the_rows_that_attend_them():
     dev["k"][0, 0, j, 5] = float("inf")
     _, _, _, g2 = step(p, dev)
     check_close("dq", np32(g2["dq"][:, :, ~sees]), np32(g["dq"][:, :, ~sees]), "f32", rel=True)
+
+
+@pytest.mark.parametrize("G,d", [(1, 64), (2, 128), (4, 64)])
+def test_f32_a_row_out_of_order_changes_no_other(G, d):
+    """A given row that names a chunk twice (entries must ascend, so its own result is nobody's
+    business) leaves the rows of its tile that hold the chunk as they were."""
+    from paper_2607_02980_amd import hils
+
+    p, _, _ = params((1, 2 * G, 2, 2 * G, 900, 960, d, 4, 64, False, False))
+    dev = to_device(host_inputs(p, 352, dout=True), p)
+    out, lse, idx, g = step(p, dev)
+    n = 704  # first of its tile
+    bad = idx.clone()
+    bad[0, 0, n] = torch.tensor([idx[0, 0, n + 16 // G - 1, 0], -1, idx[0, 0, n + 16 // G - 1, 0], -1])
+    p.flags = hils.HILS_FLAG_GIVEN_IDX
+    out2, lse2, _ = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], idx=bad)
+    p.flags = 0
+    g2 = hils.hils_bwd(p, dev["dout"], dev["q"], dev["k"], dev["v"], dev["lmk"], out, lse, bad)
+    torch.cuda.synchronize()
+    rest = torch.ones(p.N, dtype=torch.bool, device="cuda")
+    rest[n] = False
+    # (the union's order follows the rows, so the sums of the tile may run in another order)
+    for x, y, name in ((out2, out, "out"), (lse2, lse, "lse"), (g2["dq"], g["dq"], "dq")):
+        check_close(name, np32(x[:, :G, rest]), np32(y[:, :G, rest]), "f32", rel=True)
