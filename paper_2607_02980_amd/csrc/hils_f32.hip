@@ -323,28 +323,33 @@ __global__ __launch_bounds__(kAttnW * kWave, D == 64 ? 4 : 2) void k_attn_f32(Fw
                 st4(&s_o[w][col][64 * dd + 16 * lg + 4 * i],
                     f32x4{o[4 * dd][i], o[4 * dd + 1][i], o[4 * dd + 2][i], o[4 * dd + 3][i]});
         __syncthreads();
-        for (int e = tid; e < kCols * D / 4; e += (kAttnW * kWave)) {
-            const int cc = e / (D / 4), d4 = (e % (D / 4)) * 4, qq = cc / G, nn = q0 + qq;
-            if (nn >= a.N || qq < first || qq > last) continue;
-            float mm = s_m[0][cc];
+        // (the results are stored after all of the tile's are known to be finite or the pass
+        // is one query's, and the queries are read for s^: out may take their place)
+        static_assert(kCols * D / 4 <= kAttnW * kWave, "one piece of the results per thread");
+        const int cc = tid / (D / 4), d4 = (tid % (D / 4)) * 4, qq = cc / G, nn = q0 + qq;
+        const bool stores = cc < kCols && nn < a.N && qq >= first && qq <= last;
+        float mm = 0.f, zz = 0.f;
+        f32x4 acc = zero4();
+        if (stores) {
+            mm = s_m[0][cc];
 #pragma unroll
             for (int i = 1; i < kAttnW; ++i) mm = fmaxf(mm, s_m[i][cc]);
-            float zz = 0.f;
-            f32x4 acc = zero4();
 #pragma unroll
             for (int i = 0; i < kAttnW; ++i) {
                 const float x = fexp(s_m[i][cc] - mm);
                 zz += s_z[i][cc] * x;
                 acc += ld4(&s_o[i][cc][d4]) * x;
             }
-            const size_t orow = ((size_t)b * a.Hq + g * G + cc % G) * a.N + nn;
             acc *= 1.f / zz;
-            st4(as_mut<float>(a.out) + orow * D + d4, acc);
-            if (d4 == 0) a.lse[orow] = mm + __logf(zz);
             const float t = acc[0] + acc[1] + acc[2] + acc[3];
             if (NQ > 1 && !(fabsf(t) < INFINITY)) tp.bad = 1;
         }
         __syncthreads();
+        if (stores && (first == last || !tp.bad)) {
+            const size_t orow = ((size_t)b * a.Hq + g * G + cc % G) * a.N + nn;
+            st4(as_mut<float>(a.out) + orow * D + d4, acc);
+            if (d4 == 0) a.lse[orow] = mm + __logf(zz);
+        }
     };
     pass(0, NQ - 1);
     if (NQ > 1 && tp.bad)

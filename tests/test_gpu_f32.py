@@ -127,3 +127,19 @@ def test_f32_a_row_out_of_order_changes_no_other(G, d):
     # (the union's order follows the rows, so the sums of the tile may run in another order)
     for x, y, name in ((out2, out, "out"), (lse2, lse, "lse"), (g2["dq"], g["dq"], "dq")):
         check_close(name, np32(x[:, :G, rest]), np32(y[:, :G, rest]), "f32", rel=True)
+
+
+def test_f32_prefill_in_place():
+    """Outputs in the place of the queries: the bits of a separate output, also in tiles that
+    are computed again because a value they share is not finite."""
+    from paper_2607_02980_amd import hils
+
+    p, _, _ = params((1, 8, 2, 8, 700, 704, 64, 4, 64, False, False))
+    dev = to_device(host_inputs(p, 353), p)
+    dev["v"][0, 0, 130] = float("nan")
+    a = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"])
+    b = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], out=dev["q"])
+    torch.cuda.synchronize()
+    assert torch.isnan(a[0]).any() and torch.equal(a[2], b[2])
+    same = torch.equal(torch.nan_to_num(a[0], nan=1e9), torch.nan_to_num(b[0], nan=1e9)), torch.equal(a[1], b[1])
+    assert same == (True, True)
