@@ -41,46 +41,60 @@ __device__ __forceinline__ void st4(float* p, const f32x4& x) { *reinterpret_cas
 // The parts of a tile of queries q0 .. q0 + 16/G - 1 of one KV group: the 64-key pieces
 // of their local windows, then the union of the chunks they retrieved, each with the
 // queries that did.
-struct TileParts {
-    int sel[kMaxItems];               // [query][K] the rows' valid entries, else -1
+struct __align__(16) TileParts {
+    int sel[kMaxItems];               // [query][K, a multiple of 4] the rows' valid entries, else -1
     int chunk[kMaxItems];             // union, in order of (first query, slot)
     unsigned short users[kMaxItems];  // its queries, one bit each
     int wave_n[kAttnW];
+    int len[kCols];                   // entries up to the query's last valid one
     int n;                            // union size
     int bad;                          // a result of the tile is not finite
 };
 
-// Fills sel, chunk, users and n; called by the whole block, ends with a barrier.
+// Fills sel, chunk, users and n; called by the whole block, ends with a barrier.  Every valid
+// entry counts its chunk in all the queries' lists, four entries per LDS read and no further
+// than each list's last valid entry (all entries one by one, with a division for the query:
+// 142 us for 200 tokens, 4 heads in groups of 1, d = 64, K = 64, W = 64).
 template <int NW>
 __device__ inline void build_parts(TileParts& tp, const int32_t* idx, int N, int K, int W, int q0, int nq) {
     const int tid = threadIdx.x, lane = tid % kWave, w = wave_id();
-    for (int e = tid; e < nq * K; e += NW * kWave) {
-        const int n = q0 + e / K;
-        int v = -1;
-        if (n < N) {
-            const int32_t* row = idx + (size_t)n * K;
-            if (idx_entry_valid(row, e % K, n_candidates(n, W))) v = row[e % K];
-        }
-        tp.sel[e] = v;
-    }
+    const int K4 = (K + 3) & ~3;
+    if (tid < nq) tp.len[tid] = 0;
     if (tid == 0) tp.bad = 0;
     __syncthreads();
+    for (int e = tid; e < nq * K4; e += NW * kWave) {
+        const int q = e / K4, slot = e % K4, n = q0 + q;
+        int v = -1;
+        if (n < N && slot < K) {
+            const int32_t* row = idx + (size_t)n * K;
+            if (idx_entry_valid(row, slot, n_candidates(n, W))) v = row[slot];
+        }
+        tp.sel[e] = v;
+        if (v >= 0) atomicMax(&tp.len[q], slot + 1);
+    }
+    __syncthreads();
+    auto times = [&](int i, int c, int upto) {  // how often query i names c before slot upto
+        const int4* row = reinterpret_cast<const int4*>(tp.sel + i * K4);
+        int t = 0;
+        for (int s = 0; s < upto; s += 4) {
+            const int4 v = row[s / 4];
+            t += (int)(v.x == c) + (int)(v.y == c) + (int)(v.z == c) + (int)(v.w == c);
+        }
+        return t;
+    };
     int base = 0;
-    for (int e0 = 0; e0 < nq * K; e0 += NW * kWave) {
+    for (int e0 = 0; e0 < nq * K4; e0 += NW * kWave) {
         const int e = e0 + tid;
-        const int c = e < nq * K ? tp.sel[e] : -1;
+        const int c = e < nq * K4 ? tp.sel[e] : -1;
         // the m-th time that a query names the chunk (a given row out of order may name it more
         // than once): used by the queries that name it as often, listed by the first of them
-        const int q = e / K;
+        const int q = e / K4;
         unsigned users = 0;
-        if (c >= 0) {
+        if (__ballot(c >= 0) != 0ull) {  // uniform over the wave
             int m = 1;
-            for (int t = q * K; t < e; ++t) m += tp.sel[t] == c;
-            for (int i = 0; i < nq; ++i) {
-                int times = 0;
-                for (int t = i * K; t < (i + 1) * K; ++t) times += tp.sel[t] == c;
-                users |= (unsigned)(times >= m) << i;
-            }
+            for (int t = q * K4; t < e && c >= 0; ++t) m += tp.sel[t] == c;
+            for (int i = 0; i < nq; ++i)
+                users |= (unsigned)(times(i, c, __builtin_amdgcn_readfirstlane(tp.len[i])) >= m) << i;
         }
         const bool lead = c >= 0 && (users & ((1u << q) - 1u)) == 0;
         const uint64_t bal = __ballot(lead);
