@@ -22,6 +22,13 @@ CASES = [
     (2, 8, 1, 8, 450, 512, 128, 7, 200, True, True),    # G = 8: 2 queries per block
     (1, 16, 2, 2, 321, 384, 64, 5, 64, True, True),     # G = 8, shared landmarks
     (1, 2, 1, 2, 1500, 1536, 64, 4, 256, False, False),
+    # up to 112 queries: a block per query while about a round of them fits the chip, or tiles
+    (1, 4, 4, 4, 64, 64, 128, 3, 1, True, True),
+    (3, 8, 1, 1, 64, 128, 64, 3, 1, True, False),
+    (1, 4, 2, 4, 112, 128, 128, 5, 1, True, True),
+    (1, 4, 2, 2, 113, 128, 64, 5, 1, False, True),
+    (5, 16, 4, 16, 79, 128, 64, 2, 1, False, False),    # 1580 rows: tiles
+    (9, 16, 4, 16, 79, 128, 64, 2, 1, False, False),    # 2844: blocks
 ]
 
 
