@@ -801,11 +801,11 @@ __global__ __launch_bounds__(DqCfg<G>::NT, 4) void k_bwd_dq(BwdArgs a, const flo
     for (int db = 0; db < DB; ++db) {
         const int d0 = db * 16 + lg * 4;
         const f32x4 x = dq[db] * a.scale;
-        *reinterpret_cast<uint2*>(dqo + d0) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+        store_unaligned(dqo + d0, make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])));
         if constexpr (ROUTE) {
             const f32x4 y = accr[db] * a.scale;
-            *reinterpret_cast<uint2*>(as_mut<bf16>(a.dq_route) + qrow * D + d0) =
-                make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+            store_unaligned(as_mut<bf16>(a.dq_route) + qrow * D + d0,
+                            make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])));
         }
     }
 }

@@ -35,8 +35,13 @@ constexpr int kMaxItems = kCols * 64;    // entries of 16 / G queries' selection
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
-__device__ __forceinline__ void st4(float* p, const f32x4& x) { *reinterpret_cast<f32x4*>(p) = x; }
+// Four floats of global memory, of which only the alignment of a float is known (a caller's
+// array may begin anywhere; one instruction takes it all the same), and of LDS.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+__device__ __forceinline__ void st4(float* p, const f32x4& x) { *reinterpret_cast<f32x4u*>(p) = x; }
+__device__ __forceinline__ f32x4 lds4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ void to_lds4(float* p, const f32x4& x) { *reinterpret_cast<f32x4*>(p) = x; }
 
 // The parts of a tile of queries q0 .. q0 + 16/G - 1 of one KV group: the 64-key pieces
 // of their local windows, then the union of the chunks they retrieved, each with the
@@ -334,7 +339,7 @@ __global__ __launch_bounds__(kAttnW * kWave, D == 64 ? 4 : 2) void k_attn_f32(Fw
         for (int dd = 0; dd < D / 64; ++dd)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                st4(&s_o[w][col][64 * dd + 16 * lg + 4 * i],
+                to_lds4(&s_o[w][col][64 * dd + 16 * lg + 4 * i],
                     f32x4{o[4 * dd][i], o[4 * dd + 1][i], o[4 * dd + 2][i], o[4 * dd + 3][i]});
         __syncthreads();
         // (the results are stored after all of the tile's are known to be finite or the pass
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(kAttnW * kWave, D == 64 ? 4 : 2) void k_attn_f32(Fw
             for (int i = 0; i < kAttnW; ++i) {
                 const float x = fexp(s_m[i][cc] - mm);
                 zz += s_z[i][cc] * x;
-                acc += ld4(&s_o[i][cc][d4]) * x;
+                acc += lds4(&s_o[i][cc][d4]) * x;
             }
             acc *= 1.f / zz;
             const float t = acc[0] + acc[1] + acc[2] + acc[3];
@@ -510,10 +515,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_dq_f32(BwdArg
                 f32x4 x = {dq[4 * dd][i], dq[4 * dd + 1][i], dq[4 * dd + 2][i], dq[4 * dd + 3][i]};
                 const f32x4 y = {dr[4 * dd][i], dr[4 * dd + 1][i], dr[4 * dd + 2][i], dr[4 * dd + 3][i]};
                 if (route)
-                    st4(&s_r[w][col][d0], y);
+                    to_lds4(&s_r[w][col][d0], y);
                 else
                     x += y;
-                st4(&s_o[w][col][d0], x);
+                to_lds4(&s_o[w][col][d0], x);
             }
         __syncthreads();
         for (int e = tid; e < kCols * D / 4; e += kThreads) {
@@ -523,8 +528,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_dq_f32(BwdArg
             f32x4 x = zero4(), y = zero4();
 #pragma unroll
             for (int i = 0; i < kW; ++i) {
-                x += ld4(&s_o[i][cc][d4]);
-                if (route) y += ld4(&s_r[i][cc][d4]);
+                x += lds4(&s_o[i][cc][d4]);
+                if (route) y += lds4(&s_r[i][cc][d4]);
             }
             x *= a.scale;
             st4(as_mut<float>(a.dq) + orow * D + d4, x);
@@ -584,7 +589,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
     const float* go = as<float>(a.dout);
     for (int e = tid; e < 2 * kChunk * D / 4; e += kThreads) {
         const int m = e / (kChunk * D / 4), r = e % (kChunk * D / 4) / (D / 4), d4 = (e % (D / 4)) * 4;
-        st4(&s_kv[m][r][d4], ld4(as<float>(m ? a.v : a.k) + (bg * a.L + j0 + r) * D + d4));
+        to_lds4(&s_kv[m][r][d4], ld4(as<float>(m ? a.v : a.k) + (bg * a.L + j0 + r) * D + d4));
     }
     __syncthreads();
     const int n_hi = min(a.N - 1, j0 + kChunk + a.W - 2);
@@ -639,8 +644,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
                 s[k] = gv[k] = zero4();
 #pragma unroll
                 for (int tt = 0; tt < T; ++tt) {
-                    const f32x4 kk = ld4(&s_kv[0][16 * k + col][16 * tt + 4 * lg]);
-                    const f32x4 vv = ld4(&s_kv[1][16 * k + col][16 * tt + 4 * lg]);
+                    const f32x4 kk = lds4(&s_kv[0][16 * k + col][16 * tt + 4 * lg]);
+                    const f32x4 vv = lds4(&s_kv[1][16 * k + col][16 * tt + 4 * lg]);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         s[k] = mfma_f32(x[tt][j], kk[j], s[k]);
@@ -751,7 +756,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
             const int hd = G == 8 ? 4 * lg + h : h;
             if (col == 0) s_db[w][hd] = x;
 #pragma unroll
-            for (int dd = 0; dd < D / 64; ++dd) st4(&s_dl[w][hd][64 * dd + 4 * col], y[dd]);
+            for (int dd = 0; dd < D / 64; ++dd) to_lds4(&s_dl[w][hd][64 * dd + 4 * col], y[dd]);
         }
     }
     // dK, dV: the waves add their sums one after another
@@ -769,18 +774,18 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
                         f32x4 x = {dk[4 * dd][k][i], dk[4 * dd + 1][k][i], dk[4 * dd + 2][k][i], dk[4 * dd + 3][k][i]};
                         f32x4 y = {dv[4 * dd][k][i], dv[4 * dd + 1][k][i], dv[4 * dd + 2][k][i], dv[4 * dd + 3][k][i]};
                         if (ww > 0) {
-                            x += ld4(pk);
-                            y += ld4(pv);
+                            x += lds4(pk);
+                            y += lds4(pv);
                         }
-                        st4(pk, x);
-                        st4(pv, y);
+                        to_lds4(pk, x);
+                        to_lds4(pv, y);
                     }
     }
     __syncthreads();
     float* out = sums + ((bg * nC + c) * nsplit + split) * (size_t)SL::n;
     for (int e = tid; e < 2 * kChunk * D / 4; e += kThreads) {
         const int m = e / (kChunk * D / 4), r = e % (kChunk * D / 4) / (D / 4), d4 = (e % (D / 4)) * 4;
-        st4(out + (m ? SL::dv : SL::dk) + r * D + d4, ld4(&s_kv[m][r][d4]));
+        st4(out + (m ? SL::dv : SL::dk) + r * D + d4, lds4(&s_kv[m][r][d4]));
     }
     for (int e = tid; e < G * D + G; e += kThreads) {
         float x = 0.f;

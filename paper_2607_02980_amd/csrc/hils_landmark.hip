@@ -314,8 +314,8 @@ __global__ __launch_bounds__(kWave) void k_lmk_fwd_m(LmkArgs a) {
         bf16* out = as_mut<bf16>(a.lmk) + row * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
-            *reinterpret_cast<uint2*>(out + db * 16 + lg * 4) =
-                make_uint2(pack_bf16x2(o[db][0], o[db][1]), pack_bf16x2(o[db][2], o[db][3]));
+            store_unaligned(out + db * 16 + lg * 4,
+                            make_uint2(pack_bf16x2(o[db][0], o[db][1]), pack_bf16x2(o[db][2], o[db][3])));
         if (lg == 0) a.bias[row] = lse - ps;  // -sum p log p with log p = s - lse
     }
 }
@@ -398,8 +398,9 @@ __global__ __launch_bounds__(kWave) void k_lmk_bwd_m(LmkArgs a) {
             bf16* dst = as_mut<bf16>(a.dlq) + row * D;
 #pragma unroll
             for (int d = 0; d < DB; ++d)
-                *reinterpret_cast<uint2*>(dst + d * 16 + lg * 4) = make_uint2(
-                    pack_bf16x2(a.scale * o[d][0], a.scale * o[d][1]), pack_bf16x2(a.scale * o[d][2], a.scale * o[d][3]));
+                store_unaligned(dst + d * 16 + lg * 4,
+                                make_uint2(pack_bf16x2(a.scale * o[d][0], a.scale * o[d][1]),
+                                           pack_bf16x2(a.scale * o[d][2], a.scale * o[d][3])));
         }
     }
     // T[key][..]: p hi, p lo, scale ds hi, scale ds lo of head n16 (lanes n16 < 8)

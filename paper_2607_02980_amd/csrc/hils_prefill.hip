@@ -1154,7 +1154,7 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 4) void k_pf_local(FwdArgs a, cons
         for (int db = 0; db < DB; ++db) {
             const int d0 = db * 16 + lg * 4;
             const f32x4 r = o[db] * inv;
-            *reinterpret_cast<uint2*>(out + row * D + d0) = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+            store_unaligned(out + row * D + d0, make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])));
         }
         if (lane < 16) a.lse[row] = M + __logf(Z);
     }

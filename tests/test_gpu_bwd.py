@@ -79,3 +79,52 @@ def test_bwd_is_deterministic():
     torch.cuda.synchronize()
     for key in a:
         assert torch.equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("dtype,d,G,route", [("f32", 64, 4, True), ("f32", 128, 1, False), ("bf16", 64, 2, True),
+                                             ("bf16", 128, 4, False)])
+def test_arrays_aligned_to_their_elements_only(dtype, d, G, route):
+    """Outputs of the prefill and the backward, and in fp32 the inputs too, that begin one
+    element into a larger array: the same bits, and nothing around the outputs is written."""
+    import ctypes
+
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=1, Hq=2 * G, Hkv=2, N=401, L=448, d=d, topk=4, window=70, dtype=dtype)
+    log(f"[bwd] arrays one element into others: {dtype} d={d} G={G} route={route}")
+    dev = to_device(host_inputs(p, 314, bias=True, route=route, dout=True), p)
+    dev.setdefault("q_route", None)
+
+    def inner(shape, t=None):
+        n = int(np.prod(shape))
+        base = torch.full((n + 16,), 7.0, dtype=p.torch_dtype, device="cuda")
+        if t is not None:
+            base[1:1 + n] = t.reshape(-1)
+        return base[1:1 + n].view(shape)
+
+    args = [dev[n] for n in ("q", "k", "v", "lmk", "bias", "q_route")]
+    out, lse, idx = hils.hils_prefill_fwd(p, *args)
+    g = hils.hils_bwd(p, dev["dout"], *args[:4], out, lse, idx, *args[4:])
+    if dtype == "f32":
+        for n in ("q", "k", "v", "lmk", "dout", "q_route"):
+            if dev[n] is not None:
+                dev[n] = inner(dev[n].shape, dev[n])
+        args = [dev[n] for n in ("q", "k", "v", "lmk", "bias", "q_route")]
+    got = {"out": inner(out.shape)}
+    _, lse2, idx2 = hils.hils_prefill_fwd(p, *args, out=got["out"])
+    assert torch.equal(lse, lse2) and torch.equal(idx, idx2)
+    for n in ("dq", "dk", "dv", "dlmk") + (("dq_route",) if route else ()):
+        got[n] = inner(g[n].shape)
+    dbias = torch.empty_like(g["dlmk_bias"])
+    ws = torch.empty(hils.hils_workspace_size(p, hils.HILS_OP_BWD), dtype=torch.uint8, device="cuda")
+    ptr = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    rc = hils.LIB.hils_bwd(ctypes.byref(p.c()), ptr(dev["dout"]), *map(ptr, args), ptr(got["out"]), ptr(lse2), ptr(idx2),
+                           *(ptr(got[n]) for n in ("dq", "dk", "dv", "dlmk")), ptr(dbias), ptr(got.get("dq_route")),
+                           ptr(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0, hils.hils_last_error()
+    assert torch.equal(dbias, g["dlmk_bias"])
+    for n, x in got.items():
+        ref = out if n == "out" else g[n]
+        same, base = torch.equal(x, ref), x._base
+        assert same and bool((base[:1] == 7).all()) and bool((base[1 + x.numel():] == 7).all()), n

@@ -60,6 +60,21 @@ def test_no_mfma_under_unguarded_exec_mask(tmp_path):
     assert not problems, problems
 
 
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
+def test_f32_kernels_assume_no_more_than_the_alignment_of_a_float(tmp_path):
+    """The fp32 arrays of a caller may begin at any float: no access to global memory in these
+    kernels promises the compiler more (one 16-byte instruction serves it all the same)."""
+    out = os.path.join(tmp_path, "f32.ll")
+    cmd = [B.HIPCC, *B.FLAGS, "-x", "hip", "--cuda-device-only", "-emit-llvm", "-S",
+           os.path.join(B.CSRC, "hils_f32.hip"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    accesses = [ln.strip() for ln in open(out) if re.search(r"\b(load|store) .*addrspace\(1\)", ln)]
+    assert len(accesses) > 100
+    wide = [ln for ln in accesses if int(re.search(r"align (\d+)", ln).group(1)) > 4]
+    assert not wide, (len(wide), wide[:3])
+
+
 def test_checker_flags_a_masked_mfma():
     asm = [
         "_Zkernel:",
