@@ -771,9 +771,11 @@ __device__ __forceinline__ void scan_shared(const FwdArgs& a, const DecLayout& l
 // NQ new queries of one sequence share a workgroup (grid z = B x ceil(N / NQ)):
 // the landmark rows are read once for all of them; wave q selects for query q.
 // Each query row keeps its own candidate count (its own position).
+// counters: the arrival counters that the passes after the scan use and the scan clears.
 constexpr int kScanSelect = 0, kScanNormKeep = 1;
+constexpr int kNoCounters = 0, kPartCounters = 1, kMqCounters = 2;
 template <typename T, int D, int G, int NQ, bool PAGED>
-__global__ __launch_bounds__(kBlock) void k_dec_scan(FwdArgs a, DecLayout ly, int mode) {
+__global__ __launch_bounds__(kBlock) void k_dec_scan(FwdArgs a, DecLayout ly, int mode, int counters) {
     static_assert(NQ <= kBlock / kWave, "one selecting wave per query");
     const int ngrp = (a.N + NQ - 1) / NQ;
     const int b = blockIdx.z / ngrp, n0 = (blockIdx.z % ngrp) * NQ, g = blockIdx.y;
@@ -788,12 +790,13 @@ __global__ __launch_bounds__(kBlock) void k_dec_scan(FwdArgs a, DecLayout ly, in
     auto len_of = [&](int q) {
         return q < nq ? max(0, min(ly.slice, n_candidates(decode_position(a, b, n0 + q), a.W) - c0)) : 0;
     };
-    // the arrival counters of the passes that follow (at the end of the scan: a store
-    // before its loads took 2 us of the 85 us scan of 32 sequences of 131K)
+    // (at the end of the scan: a store before its loads took 2 us of the 85 us scan of 32
+    // sequences of 131K; clearing counters that no pass uses 0.2 of that step's 131 us)
     auto clear_counters = [&]() {
-        if (blockIdx.x != 0 || tid != 0) return;
-        for (int q = 0; q < nq; ++q) *part_counter<D>(a, ly, row_of(q), G) = 0;
-        if (a.N > 1 && n0 == 0) {
+        if (counters == kNoCounters || blockIdx.x != 0 || tid != 0) return;
+        if (counters == kPartCounters) {
+            for (int q = 0; q < nq; ++q) *part_counter<D>(a, ly, row_of(q), G) = 0;
+        } else if (n0 == 0) {
             const int nqg = 16 / G < 8 ? 16 / G : 8, ng = (a.N + nqg - 1) / nqg;
             for (int i = 0; i < ng; ++i) *mq_counter(a, ly, (b * ng + i) * a.Hkv + g) = 0;
         }
@@ -2011,12 +2014,13 @@ struct DecRun {
     template <typename T, int D, int G>
     static hipError_t run(const FwdArgs& a, hipStream_t s) {
         const int R = a.B * a.N;  // rows (sequence, new query); the host keeps R <= 65535
+        const int cus = device_cus();
         const DecLayout ly = dec_layout(a.B, a.N, a.Hkv, G, D, a.L, a.K, a.W, a.head_norm);
         if constexpr (sizeof(T) == 2) {
             // short caches, one new query per sequence, a workgroup per row in one round of
             // the CUs: scan, selection, parts and fusion in one launch
             if (a.N == 1 && !a.given_idx && !a.head_norm && ly.nC <= kSlice &&
-                R * a.Hkv >= kRowPassMinRows && R * a.Hkv <= device_cus()) {
+                R * a.Hkv >= kRowPassMinRows && R * a.Hkv <= cus) {
                 const dim3 rgrid(a.Hkv, R), rblock(kRowWaves * kWave);
                 if (a.q_route)
                     HILS_LAUNCH("k_dec_row", (k_dec_row<D, G, kScanInRow, true>), rgrid, rblock, 0, s, a, ly);
@@ -2025,6 +2029,22 @@ struct DecRun {
                 return hipGetLastError();
             }
         }
+        // the pass after the scan (bf16): several new queries per sequence in groups of NQ, a
+        // workgroup per row, or a wave per part
+        constexpr int NQ = MqCfg<G>::NQ;
+        const int rows = R * a.Hkv;
+        const bool mq_pass = sizeof(T) == 2 && a.N > 1 && ly.mq_umax <= kMqMaxUnion;
+        const bool row_pass = sizeof(T) == 2 && !mq_pass && rows >= kRowPassMinRows && rows <= cus;
+        // (given idx: no scan has cleared the counters)
+        const int nsplit =
+            mq_pass && !a.given_idx ? std::max(1, std::min(8, cus / (a.Hkv * a.B * ((a.N + NQ - 1) / NQ)))) : 1;
+        // Up to one part per wave slot of the chip (8 per CU) the last workgroup of a
+        // row fuses it, which saves a launch; with more, the wait for the records'
+        // way to memory holds slots that the next parts need, and the fusion is a
+        // launch of its own (9600 parts: 112 us fused, 106 us apart).
+        const bool fuse = sizeof(T) == 2 && !mq_pass && !row_pass && !a.given_idx &&
+                          (long)rows * ly.nparts <= 8l * cus;
+        const int counters = nsplit > 1 ? kMqCounters : fuse ? kPartCounters : kNoCounters;
         if (!a.given_idx) {
             // one new query per sequence: a workgroup per (slice, group, row); several:
             // the sequence's queries four at a time share each landmark read
@@ -2032,15 +2052,19 @@ struct DecRun {
                 if (a.N == 1) {
                     const dim3 grid(ly.nslices, a.Hkv, R);
                     if (a.block_table)
-                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 1, true>), grid, dim3(kBlock), 0, s, a, ly, mode);
+                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 1, true>), grid, dim3(kBlock), 0, s, a, ly, mode,
+                                    counters);
                     else
-                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 1, false>), grid, dim3(kBlock), 0, s, a, ly, mode);
+                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 1, false>), grid, dim3(kBlock), 0, s, a, ly, mode,
+                                    counters);
                 } else {
                     const dim3 grid(ly.nslices, a.Hkv, a.B * ((a.N + 3) / 4));
                     if (a.block_table)
-                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 4, true>), grid, dim3(kBlock), 0, s, a, ly, mode);
+                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 4, true>), grid, dim3(kBlock), 0, s, a, ly, mode,
+                                    counters);
                     else
-                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 4, false>), grid, dim3(kBlock), 0, s, a, ly, mode);
+                        HILS_LAUNCH("k_dec_scan", (k_dec_scan<T, D, G, 4, false>), grid, dim3(kBlock), 0, s, a, ly, mode,
+                                    counters);
                 }
             };
             if (a.head_norm) {
@@ -2061,13 +2085,7 @@ struct DecRun {
         }
         if constexpr (sizeof(T) == 2) {
             const int surv = ly.nslices * a.K;  // the scan's survivors per row
-            const int rows = R * a.Hkv;
-            constexpr int NQ = MqCfg<G>::NQ;
-            if (a.N > 1 && ly.mq_umax <= kMqMaxUnion) {
-                // several new queries per sequence: a workgroup per group of NQ of them
-                const int groups = a.Hkv * a.B * ((a.N + NQ - 1) / NQ);
-                // (given idx: no scan has cleared the groups' counters)
-                const int nsplit = a.given_idx ? 1 : std::max(1, std::min(8, device_cus() / groups));
+            if (mq_pass) {
                 const dim3 mgrid(a.Hkv, a.B * ((a.N + NQ - 1) / NQ), nsplit), mblock(kRowWaves * kWave);
                 auto mq = [&](auto e_tag) {
                     constexpr int EE = decltype(e_tag)::value;
@@ -2086,7 +2104,7 @@ struct DecRun {
                     mq(std::integral_constant<int, 4>{});
                 else
                     mq(std::integral_constant<int, 16>{});
-            } else if (rows >= kRowPassMinRows && rows <= device_cus()) {
+            } else if (row_pass) {
                 // a workgroup per row; one merge round covers kRowWaves * 64 * E survivors
                 const dim3 rgrid(a.Hkv, R), rblock(kRowWaves * kWave);
                 auto row = [&](auto e_tag) {
@@ -2103,13 +2121,8 @@ struct DecRun {
                 else
                     row(std::integral_constant<int, 16>{});
             } else {
-                // Up to one part per wave slot of the chip (8 per CU) the last workgroup of a
-                // row fuses it, which saves a launch; with more, the wait for the records'
-                // way to memory holds slots that the next parts need, and the fusion is a
-                // launch of its own (9600 parts: 112 us fused, 106 us apart).
                 constexpr int WPB = kBlock / kWave;
                 const dim3 pgrid((ly.nparts + WPB - 1) / WPB, a.Hkv, R);
-                const bool fuse = !a.given_idx && (long)rows * ly.nparts <= 8l * device_cus();
                 auto parts = [&](auto e_tag) {
                     constexpr int EE = decltype(e_tag)::value;
                     if constexpr (EE > 0) {
