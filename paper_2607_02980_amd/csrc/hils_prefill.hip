@@ -1201,14 +1201,18 @@ struct PfRun {
         const int nC = a.L / kChunk;
         // With no more tiles than the chip takes at once (two per CU) a union is one chain of
         // barriers, 2.2 us per chunk at d = 128 and 1.6 at 64 however few the tiles, and the
-        // chunk-major pass spreads over the chunks: one sequence, union and chunk-major in us:
-        // 26 chunks, K = 16, 8 heads: 71 and 95; 38, K = 4, groups of 1, 2 and 4 (8, 16 and 4
-        // heads): 96 and 72, 96 and 86, 91 and 78; 83, K = 16, 8 and 4 heads: 210 and 179,
-        // 190 and 125 (16 heads, 662 tiles: 236 and 285).
-        const bool one_round = (size_t)a.B * a.Hkv * ((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT) <=
-                               2 * (size_t)device_cus();
+        // chunk-major pass spreads over the chunks: its time grows with tiles * K, slowly while
+        // the chip is not full.  Whole calls, union and chunk-major in us, one sequence, d =
+        // 128, groups of 1: K = 4, 4 heads: 14 chunks 43 and 45, 26 chunks 69 and 49; K = 16, 46
+        // chunks: 1 head 112 and 69, 16 heads 133 and 146.  The line was fitted to 1900
+        // such pairs (1 to 16 KV heads, groups of 1 to 8, K = 1 to 64, 10 to 260 chunks): on the
+        // mean 0.2 % over the faster way with i.i.d. queries and 0.5 % with AR(1) ones of rho
+        // 0.97 (a line of K + 24 chunks: 2.5 and 2.7 %, at worst twice the time).
+        const size_t tiles = (size_t)a.B * a.Hkv * ((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT);
+        const bool one_round = tiles <= 2 * (size_t)device_cus();
         const int few = D == 128 ? 4 * a.K + 24 : 3 * a.K + 16;
-        const bool few_chunks = !a.union_pack && nC <= (one_round ? std::min(few, a.K + 24) : few);
+        const int few_one_round = (D == 128 ? 10 : 14) + 3 * G + a.K / 2 + (int)(tiles * a.K / 160);
+        const bool few_chunks = !a.union_pack && nC <= (one_round ? std::min(few, few_one_round) : few);
         bool cleared = false;  // the inverse index's counters
         if (!a.given_idx) {
             const dim3 grid((unsigned)((a.N + kSQ - 1) / kSQ) * a.Hkv * a.B);

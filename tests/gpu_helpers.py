@@ -82,6 +82,18 @@ def np32(t):
     return t.detach().float().cpu().numpy() if isinstance(t, torch.Tensor) else t
 
 
+def kernels_of(call) -> set:
+    """Names of the library kernels that a call launches."""
+    from paper_2607_02980_amd import hils
+
+    hils.hils_timing_enable(True)
+    try:
+        call()
+        return set(hils.hils_timing_read())
+    finally:
+        hils.hils_timing_enable(False)
+
+
 def check_selection(p, host: dict, gpu_idx: np.ndarray, ref_idx: np.ndarray, qpos=None, rows=None):
     """Tie-aware comparison.  Returns the number of rows that differed (all accepted)."""
     s = oshape(p)

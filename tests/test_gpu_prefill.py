@@ -10,7 +10,8 @@ import torch
 
 import oracle
 from paper_2607_02980_amd import synth
-from tests.gpu_helpers import (check_close, check_lse, check_selection, host_inputs, log, np32, oshape, to_device)
+from tests.gpu_helpers import (check_close, check_lse, check_selection, host_inputs, kernels_of, log, np32, oshape,
+                               to_device)
 
 pytestmark = pytest.mark.gpu
 
@@ -188,11 +189,12 @@ def test_prefill_is_deterministic():
 @pytest.mark.parametrize("N,Hkv,G,K,rho", [(830, 2, 4, 4, 0.0), (1790, 2, 4, 4, 0.97), (1800, 1, 4, 4, 0.0),
                                            (1330, 1, 8, 6, 0.0), (770, 3, 1, 4, 0.0), (1850, 3, 1, 4, 0.0),
                                            (1025, 1, 2, 4, 0.0), (1000, 2, 2, 64, 0.0),
-                                           (2040, 1, 4, 8, 0.0), (2100, 1, 4, 8, 0.0),   # one round: 32 and 33 chunks
+                                           (2040, 1, 4, 8, 0.0), (2100, 1, 4, 8, 0.0),
+                                           (2360, 1, 4, 8, 0.0), (2400, 1, 4, 8, 0.0),   # one round: 37 and 38 chunks
                                            (2550, 4, 4, 8, 0.0), (2610, 4, 4, 8, 0.0)])  # more tiles: 40 and 41
 def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
     """Few more chunks than a row retrieves (the union path; on both sides of its limit,
-    3 K + 16 chunks at d = 64, K + 24 while the tiles fit the chip at once) against the same
+    3 K + 16 chunks at d = 64, fewer while the tiles fit the chip at once) against the same
     selection given with a gap before it, which always takes the chunk-major pass, and
     without one, which takes the same path; and a NaN value stays with the rows that attend it."""
     from paper_2607_02980_amd import hils
@@ -227,6 +229,22 @@ def test_few_chunks_match_given_selection(N, Hkv, G, K, rho):
     assert torch.equal(idx, idx2)
     far = ~sees & ~near
     assert torch.equal(out2[0, :G, far], out[0, :G, far]) and torch.isnan(out2[0, :G, sees]).all()
+
+
+@pytest.mark.parametrize("N,Hkv,G,K,union", [(700, 4, 1, 2, True), (1441, 4, 1, 2, False),    # 44 and 62 us: records, union
+                                             (1534, 4, 1, 4, False), (2933, 1, 1, 16, False),  # 46 chunks: 69 and 112 us
+                                             (2933, 16, 1, 16, True),                          # 146 and 133 us
+                                             (1200, 2, 4, 4, True), (2600, 2, 4, 4, False),
+                                             (2600, 2, 8, 8, True)])
+def test_few_tiles_take_the_faster_way(N, Hkv, G, K, union):
+    """One sequence of few tiles (d = 128): the union pass while it is the shorter chain, the
+    chunk-major pass, which spreads over the chunks, beyond."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=1, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=128, topk=K, window=64)
+    dev = to_device(host_inputs(p, 374), p)
+    ran = kernels_of(lambda: hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"]))
+    assert ("k_pf_union" in ran, "k_pf_chunks" in ran) == (union, not union), ran
 
 
 @pytest.mark.parametrize("N,Hkv,G,K,d", [(6200, 2, 4, 16, 128), (5700, 1, 8, 17, 128), (6000, 1, 4, 20, 128),
