@@ -1268,8 +1268,8 @@ struct PfRun {
                             (const bf16*)nullptr, (const float*)nullptr, 0, a.N, (const uint8_t*)nullptr);
             return hipGetLastError();
         }
-        // Otherwise, with d = 128, groups of 4 or 8, K >= 16 and more tiles than one round, each tile takes the cheaper
-        // way by the size of its union, which the index counts: the records of a tile cost 310
+        // Otherwise, with d = 128, groups of 4 or 8, K >= 16 and more tiles than one round, each
+        // tile takes the cheaper way by the size of its union, which the index counts: the records of a tile cost 310
         // to 410 ns at K = 16, a union chunk 7 (groups of 4) or 5 (of 8).  Early tiles have few
         // candidates, and the queries of trained models retrieve alike.  32 heads, K = 16, all
         // tiles chunk-major and by tile: 8000 tokens in groups of 4, i.i.d. 749 and 701 us, AR(1)
@@ -1280,7 +1280,17 @@ struct PfRun {
         // 64 (246 and 286).  (A given selection takes the same way as one made here, tile by
         // tile, except that the union does not look past gaps in a row: such tiles stay
         // chunk-major.)
-        const bool per_tile = nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16 && !one_round));
+        // And of the KV groups of all sequences there have to be enough that the early tiles,
+        // which take the union with any queries, fill the chip; as fewer they are one more chain,
+        // of up to umax chunks.  All chunk-major and by tile, i.i.d. queries, K = 16, 20000
+        // tokens, groups of 4: 1, 2, 4 and 8 KV heads 347 and 445, 616 and 703, 1146 and 1203,
+        // 1972 and 1942 us (11000, K = 32, 4 heads: 992 and 943); groups of 8: 1 head, 11000
+        // tokens 354 and 446, 2 heads 623 and 649, 4 heads 1146 and 1112 (with rho 0.97: 1 head
+        // 347 and 292, 2 heads 601 and 406).
+        const size_t groups = (size_t)a.B * a.Hkv;
+        const bool fills = G == 8 ? groups >= 2 : groups >= 4 && groups * a.K >= 128;
+        const bool per_tile =
+            nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16 && !one_round && fills));
         uint8_t* flags = per_tile ? reinterpret_cast<uint8_t*>(ws + ly.flags) : nullptr;
         const int umax = few_chunks ? nC : G == 8 ? 4 * a.K : 5 * a.K / 2;
         const int* boff = reinterpret_cast<const int*>(ws + ly.inv.boff);

@@ -247,6 +247,23 @@ def test_few_tiles_take_the_faster_way(N, Hkv, G, K, union):
     assert ("k_pf_union" in ran, "k_pf_chunks" in ran) == (union, not union), ran
 
 
+@pytest.mark.parametrize("B,N,Hkv,G,K,by_tile", [(1, 17000, 1, 4, 16, False),  # 1.28 times the time by tile
+                                                 (1, 8000, 3, 4, 16, False), (1, 11000, 4, 4, 31, False),
+                                                 (2, 11000, 2, 4, 32, True), (1, 6200, 8, 4, 16, True),
+                                                 (1, 11000, 1, 8, 16, False), (2, 6200, 1, 8, 16, True)])
+def test_tiles_choose_where_the_early_ones_fill_the_chip(B, N, Hkv, G, K, by_tile):
+    """Long sequences (d = 128, more tiles than the chip takes at once): by tile with enough KV
+    groups, else all chunk-major."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=B, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=128, topk=K, window=64)
+    dev = {n: torch.randn(s, device="cuda").to(torch.bfloat16)
+           for n, s in dict(q=(B, p.Hq, N, 128), k=(B, Hkv, p.L, 128), v=(B, Hkv, p.L, 128),
+                            lmk=(B, p.Hq, p.L // 64, 128)).items()}
+    ran = kernels_of(lambda: hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"]))
+    assert "k_pf_chunks" in ran and ("k_pf_union" in ran) == by_tile, ran
+
+
 @pytest.mark.parametrize("N,Hkv,G,K,d", [(6200, 2, 4, 16, 128), (5700, 1, 8, 17, 128), (6000, 1, 4, 20, 128),
                                          (4100, 2, 1, 16, 64),
                                          # more tiles than two per CU, where the two kinds mix
