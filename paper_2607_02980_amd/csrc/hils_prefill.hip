@@ -1210,7 +1210,16 @@ struct PfRun {
         // 0.97 (a line of K + 24 chunks: 2.5 and 2.7 %, at worst twice the time).
         const size_t tiles = (size_t)a.B * a.Hkv * ((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT);
         const bool one_round = tiles <= 2 * (size_t)device_cus();
-        const int few = D == 128 ? 4 * a.K + 24 : 3 * a.K + 16;
+        const int qk = LocalCfg<G>::QT * a.K;
+        auto union_lists = [&](int most) {  // bytes of the union's lists (dynamic LDS)
+            return (size_t)((nC + 31) / 32 + qk + std::min(std::min(nC, qk), most)) * sizeof(int);
+        };
+        // At d = 128 and K = 64 (in groups of 1 from 32 on) the lists leave room for one union
+        // workgroup per CU only, and the line is lower: 32 heads in groups of 4, K = 64, 270
+        // chunks: 4.71 ms chunk-major before, 5.43 ms union, 4.33 ms by tile; 200 chunks, groups
+        // of 2 and 1 (16 and 8 heads): 1.86 and 1.12 ms chunk-major, 1.61 and 0.89 union.
+        const bool two = D == 64 || union_lists(nC) <= (size_t)(80 * 1024 - (71684 + 520 * G));  // (the static LDS)
+        const int few = D == 64 ? 3 * a.K + 16 : two ? 4 * a.K + 24 : 3 * a.K + 32;
         const int few_one_round = (D == 128 ? 10 : 14) + 3 * G + a.K / 2 + (int)(tiles * a.K / 160);
         const bool few_chunks = !a.union_pack && nC <= (one_round ? std::min(few, few_one_round) : few);
         bool cleared = false;  // the inverse index's counters
@@ -1256,8 +1265,7 @@ struct PfRun {
             }
         }
         const dim3 lgrid((unsigned)((a.N + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT) * a.Hkv * a.B);
-        const int qk = LocalCfg<G>::QT * a.K;
-        const size_t dyn = (size_t)((nC + 31) / 32 + qk + min(nC, qk)) * sizeof(int);  // the union's lists
+        const size_t dyn = union_lists(nC);
         if (a.union_pack || (few_chunks && !a.given_idx)) {
             // one-load-multiple-compute: no inverse index, no per-slot partials
             if (a.q_route)
@@ -1293,6 +1301,7 @@ struct PfRun {
             nC <= kInvHist && (few_chunks || (D == 128 && G >= 4 && a.K >= 16 && !one_round && fills));
         uint8_t* flags = per_tile ? reinterpret_cast<uint8_t*>(ws + ly.flags) : nullptr;
         const int umax = few_chunks ? nC : G == 8 ? 4 * a.K : 5 * a.K / 2;
+        const size_t tdyn = union_lists(umax);  // (a flagged tile's union is no larger)
         const int* boff = reinterpret_cast<const int*>(ws + ly.inv.boff);
         const int* list = reinterpret_cast<const int*>(ws + ly.inv.list);
         const int4* work = reinterpret_cast<const int4*>(ws + ly.inv.work);
@@ -1311,10 +1320,10 @@ struct PfRun {
             const dim3 sgrid((Ns + LocalCfg<G>::QT - 1) / LocalCfg<G>::QT, a.Hkv, a.B);
             const dim3 ugrid(sgrid.x * a.Hkv * a.B);
             if (flags && a.q_route)
-                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, true>), ugrid, dim3(LocalCfg<G>::NT), dyn, s, a,
+                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, true>), ugrid, dim3(LocalCfg<G>::NT), tdyn, s, a,
                             (const bf16*)nullptr, (const float*)nullptr, n0, Ns, (const uint8_t*)flags);
             else if (flags)
-                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, false>), ugrid, dim3(LocalCfg<G>::NT), dyn, s, a,
+                HILS_LAUNCH("k_pf_union", (k_pf_local<D, G, true, false>), ugrid, dim3(LocalCfg<G>::NT), tdyn, s, a,
                             (const bf16*)nullptr, (const float*)nullptr, n0, Ns, (const uint8_t*)flags);
             HILS_LAUNCH("k_pf_local", (k_pf_local<D, G, false, false>), sgrid, dim3(LocalCfg<G>::NT), 0, s, a,
                         (const bf16*)part, (const float*)wgt, n0, Ns, (const uint8_t*)flags);

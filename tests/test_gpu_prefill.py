@@ -247,6 +247,21 @@ def test_few_tiles_take_the_faster_way(N, Hkv, G, K, union):
     assert ("k_pf_union" in ran, "k_pf_chunks" in ran) == (union, not union), ran
 
 
+@pytest.mark.parametrize("N,Hkv,G,K,chunks", [(14200, 2, 4, 64, False), (14400, 2, 4, 64, True),  # 222 and 225 chunks
+                                              (8100, 8, 1, 32, False), (8300, 8, 1, 32, True)])   # 127 and 130
+def test_large_k_leaves_one_union_workgroup_per_cu(N, Hkv, G, K, chunks):
+    """d = 128 and lists of chunks so long that one union workgroup fits a CU: the whole call
+    takes the union up to 3 K + 32 chunks."""
+    from paper_2607_02980_amd import hils
+
+    p = hils.Params(B=1, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=128, topk=K, window=64)
+    dev = {n: torch.randn(s, device="cuda").to(torch.bfloat16)
+           for n, s in dict(q=(1, p.Hq, N, 128), k=(1, Hkv, p.L, 128), v=(1, Hkv, p.L, 128),
+                            lmk=(1, p.Hq, p.L // 64, 128)).items()}
+    ran = kernels_of(lambda: hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"]))
+    assert ("k_pf_chunks" in ran) == chunks, ran
+
+
 @pytest.mark.parametrize("B,N,Hkv,G,K,by_tile", [(1, 17000, 1, 4, 16, False),  # 1.28 times the time by tile
                                                  (1, 8000, 3, 4, 16, False), (1, 11000, 4, 4, 31, False),
                                                  (2, 11000, 2, 4, 32, True), (1, 6200, 8, 4, 16, True),
