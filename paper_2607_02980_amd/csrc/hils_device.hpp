@@ -148,7 +148,7 @@ __device__ __forceinline__ int popc64(uint64_t m) { return __popcll(m); }
 // ---- chunk geometry (Sec. 2.1) ------------------------------------------
 
 // |C_i| = l(i)/S for a query at position i, with l(i) clamped at 0.
-__device__ __forceinline__ int n_candidates(int i, int W) {
+__host__ __device__ __forceinline__ int n_candidates(int i, int W) {
     int t = i - W + 1;
     if (t < 0) return 0;
     return t / kChunk;

@@ -235,7 +235,7 @@ __device__ __forceinline__ void add_columns(const float* row0, int rows, const f
 // ---------------------------------------------------------------------------
 // Forward: local window, retrieved chunks and their fusion (Eqs. (1), (10))
 // ---------------------------------------------------------------------------
-// One block per 16 / G queries x G heads of one KV group; wave w takes parts w, w + 4,
+// One block per 16 / G queries x G heads of one KV group; wave w takes parts w, w + 8,
 // ... and keeps a running maximum M, denominator Z and numerator o per column (a window
 // piece enters with its exponentials, a chunk with e^{s^} times its own softmax), merged
 // over the waves at the end.  K and V come straight from L2: a wave shares them with no
@@ -594,8 +594,11 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void k_bwd_keys_f32(BwdA
     __syncthreads();
     const int n_hi = min(a.N - 1, j0 + kChunk + a.W - 2);
     const int nlocal = max(0, n_hi - j0 + 1);
-    const int beg = __builtin_amdgcn_readfirstlane(offsets[bg * (nC + 1) + c]);
-    const int nret = __builtin_amdgcn_readfirstlane(offsets[bg * (nC + 1) + c + 1]) - beg;
+    int beg = 0, nret = 0;
+    if (offsets) {
+        beg = __builtin_amdgcn_readfirstlane(offsets[bg * (nC + 1) + c]);
+        nret = __builtin_amdgcn_readfirstlane(offsets[bg * (nC + 1) + c + 1]) - beg;
+    }
     const int* seg = sorted + bg * a.N * a.K + beg;
     const int tloc = (nlocal + RT - 1) / RT, tiles = tloc + (nret + RT - 1) / RT;
 
@@ -891,14 +894,21 @@ struct BwdRun {
         float* sums = reinterpret_cast<float*>(ws + ly.sums);
         int* sorted = reinterpret_cast<int*>(ws + ly.sorted);
         const int nC = a.L / kChunk;
-        const InvArgs ia{a.idx, a.B, a.Hkv, a.N, a.K, a.W, a.L, 0, a.N};
+        // Sequences so short that no row has a candidate need no index: 1 to 6 tokens took 37 to
+        // 58 us with its four launches, 24 to 49 by the kernels
+        // of one block per row; without them 30 (d = 64) and 46 to 54 (d = 128).
+        const bool retrieves = n_candidates(a.N - 1, a.W) > 0;
+        const int* offsets = retrieves ? reinterpret_cast<const int*>(ws + ly.inv.offsets) : nullptr;
         HILS_LAUNCH("k_bwd_dq_f32", (k_bwd_dq_f32<D, G>), dim3((a.N + NQ - 1) / NQ, a.Hkv, a.B), dim3(kThreads), 0, s,
-                    a, u, reinterpret_cast<int*>(ws + ly.inv.counts), inv_count_words(a.B, a.Hkv, a.L, ly.inv));
-        launch_inverse_index(ia, ly.inv, a.ws, s, false, true);
-        launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
+                    a, u, reinterpret_cast<int*>(ws + ly.inv.counts),
+                    retrieves ? inv_count_words(a.B, a.Hkv, a.L, ly.inv) : 0);
+        if (retrieves) {
+            const InvArgs ia{a.idx, a.B, a.Hkv, a.N, a.K, a.W, a.L, 0, a.N};
+            launch_inverse_index(ia, ly.inv, a.ws, s, false, true);
+            launch_inv_sort(ia, ly.inv, a.ws, sorted, s);
+        }
         HILS_LAUNCH("k_bwd_keys_f32", (k_bwd_keys_f32<D, G>), dim3(nC * ly.nsplit, a.Hkv, a.B), dim3(kThreads), 0, s,
-                    a, reinterpret_cast<const int*>(ws + ly.inv.offsets), (const int*)sorted, (const float*)u, sums,
-                    ly.nsplit);
+                    a, offsets, (const int*)sorted, (const float*)u, sums, ly.nsplit);
         HILS_LAUNCH("k_bwd_sum_f32", (k_bwd_sum_f32<D, G>), dim3((SL::n / 4 + kThreads - 1) / kThreads * nC, a.Hkv, a.B),
                     dim3(kThreads), 0, s, a, (const float*)sums, ly.nsplit);
         return hipGetLastError();

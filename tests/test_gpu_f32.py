@@ -7,7 +7,8 @@ import pytest
 import torch
 
 import oracle
-from tests.gpu_helpers import check_close, check_lse, check_selection, host_inputs, log, np32, oshape, to_device
+from tests.gpu_helpers import (check_close, check_lse, check_selection, host_inputs, kernels_of, log, np32, oshape,
+                               to_device)
 
 pytestmark = pytest.mark.gpu
 
@@ -29,6 +30,10 @@ CASES = [
     (1, 4, 2, 2, 113, 128, 64, 5, 1, False, True),
     (5, 16, 4, 16, 79, 128, 64, 2, 1, False, False),    # 1580 rows: tiles
     (9, 16, 4, 16, 79, 128, 64, 2, 1, False, False),    # 2844: blocks
+    # no row has a candidate, and the first length at which one has
+    (2, 8, 4, 4, 3, 64, 128, 4, 256, True, True),
+    (1, 4, 2, 4, 64, 64, 64, 3, 1, True, False),
+    (1, 4, 2, 4, 65, 128, 64, 3, 1, True, True),
 ]
 
 
@@ -79,6 +84,17 @@ def test_f32_matches_oracle(case):
                       ("dq_route", "dq_route")):
         if rb[rkey] is not None:
             check_close(key, np32(g[key]), rb[rkey], "f32", rel=True)
+
+
+@pytest.mark.parametrize("N,W,index", [(3, 256, False), (64, 1, False), (65, 1, True), (575, 512, False), (576, 512, True)])
+def test_f32_backward_indexes_only_where_rows_retrieve(N, W, index):
+    from paper_2607_02980_amd import hils
+
+    p, _, _ = params((1, 4, 1, 4, N, -(-N // 64) * 64, 64, 4, W, False, False))
+    dev = to_device(host_inputs(p, 354, dout=True), p)
+    out, lse, idx = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"])
+    ran = kernels_of(lambda: hils.hils_bwd(p, dev["dout"], dev["q"], dev["k"], dev["v"], dev["lmk"], out, lse, idx))
+    assert ("k_inv_count" in ran, "k_inv_sort" in ran) == (index, index), ran
 
 
 def test_f32_is_deterministic():
