@@ -81,7 +81,7 @@ def prefill_kernel_model(B, Hq, Hkv, N, L, d, S, K, W, elem=2):
                  the surrogate score (2d); reads q and the K/V once.
     k_pf_local : window QK^T + PV, 4d per (row, head, window key), and the fusion;
                  reads q and K/V once, writes out and lse.  (The tiles with small
-                 unions do both in k_pf_union: main() moves their share there.)
+                 unions do both in k_pf_union: split_union moves their share there.)
     design_bytes: the records k_pf_chunks writes and k_pf_local reads back (the bf16
                  chunk output and the fp32 score per (row, head, slot)).
     """
@@ -205,7 +205,7 @@ def chunk_overlap(idx, M=16):
 def union_share(idx, G, most):
     """The tiles of 128 / G rows whose union counts at most `most` chunks, which the prefill
     computes in k_pf_union instead of the chunk-major pass: (share of the tiles, share of
-    the retrieved (row, chunk) pairs in them).  32K at groups of 4: most = 5 K / 2."""
+    the retrieved (row, chunk) pairs in them)."""
     B, Hkv, N, K = idx.shape
     QT = 128 // G
     blk = np.sort(idx[:, :, :N // QT * QT].reshape(-1, QT * K), axis=-1)
@@ -213,6 +213,22 @@ def union_share(idx, G, most):
     small = uniq <= most
     pairs = (blk >= 0).sum(axis=-1)
     return float(small.mean()), float(pairs[small].sum() / max(1, pairs.sum()))
+
+
+def union_limit(G, K):
+    """Most chunks of a tile's union that the prefill's choice by tile computes in k_pf_union."""
+    return 4 * K if G == 8 else 5 * K // 2
+
+
+def split_union(model, tiles, pairs):
+    """Moves the work of the tiles that choose the union (union_share) from the chunk and the
+    local pass's entries of a prefill_kernel_model to one of k_pf_union."""
+    chunk, local = dict(model["k_pf_chunks"]), dict(model["k_pf_local"])
+    union = {"flop": pairs * chunk["flop"] + tiles * local["flop"], "bytes": tiles * local["bytes"]}
+    chunk.update(flop=(1 - pairs) * chunk["flop"], design_bytes=(1 - pairs) * chunk["design_bytes"])
+    local.update(flop=(1 - tiles) * local["flop"], bytes=(1 - tiles) * local["bytes"],
+                 design_bytes=chunk["design_bytes"])
+    return dict(model, k_pf_chunks=chunk, k_pf_local=local, k_pf_union=union)
 
 
 def bench_prefill(torch, hils, synth, W_, steps, warmup, flags=0, rho=None):
@@ -249,7 +265,7 @@ def bench_prefill(torch, hils, synth, W_, steps, warmup, flags=0, rho=None):
     for k in kernels.values():
         k["avg_ms"] = k["total_ms"] / max(1, k["launches"])
     p.overlap16 = chunk_overlap(idx.cpu().numpy(), 16) if p.topk <= 64 and p.dtype == "bf16" else float("nan")
-    p.union_share = union_share(idx.cpu().numpy(), p.Hq // p.Hkv, 5 * p.topk // 2) if p.dtype == "bf16" else (0.0, 0.0)
+    p.union_share = union_share(idx.cpu().numpy(), p.Hq // p.Hkv, union_limit(p.Hq // p.Hkv, p.topk)) if p.dtype == "bf16" else (0.0, 0.0)
     p.ms_mean = ms_mean
     del dev, ws
     torch.cuda.empty_cache()
@@ -445,7 +461,7 @@ def run_part(part, torch, hils, synth, WORKLOADS, args):
         for name, W_, fl, rho in (("prefill_head_norm", Wp, hils.HILS_FLAG_HEAD_NORM_SELECT, None),
                                   ("prefill_mha_G1", Wp.with_(Hkv=Wp.Hq), 0, None),
                                   ("prefill_union_packing", Wp, U, None),
-                                  ("prefill_locality_chunk_major", Wp, 0, 0.97),
+                                  ("prefill_locality", Wp, 0, 0.97),
                                   ("prefill_locality_union_packing", Wp, U, 0.97)):
             pv, _, msv, kv = bench_prefill(torch, hils, synth, W_, args.steps, args.warmup, flags=fl, rho=rho)
             out[name] = {"ms_per_step": round(msv, 4), "chunk_overlap_16": round(pv.overlap16, 4),
@@ -492,12 +508,11 @@ def main():
         return
     p, host, ms, kernels = bench_prefill(torch, hils, synth, Wp, args.steps, args.warmup)
     model = prefill_kernel_model(p.B, p.Hq, p.Hkv, p.N, p.L, p.d, p.chunk, p.topk, p.window)
-    # the tiles with small unions leave the chunk-major pass: their share of the work
-    tiles, pairs = p.union_share
-    chunk, local = model["k_pf_chunks"], model["k_pf_local"]
-    model["k_pf_union"] = {"flop": pairs * chunk["flop"] + tiles * local["flop"], "bytes": tiles * local["bytes"]}
-    chunk.update(flop=(1 - pairs) * chunk["flop"], design_bytes=(1 - pairs) * chunk["design_bytes"])
-    local.update(flop=(1 - tiles) * local["flop"], design_bytes=chunk["design_bytes"])
+    # the tiles with small unions leave the chunk-major pass, where the library chooses by tile
+    by_tile = "k_pf_union" in kernels and "k_pf_chunks" in kernels
+    tiles, pairs = p.union_share if by_tile else (0.0, 0.0)
+    if by_tile:
+        model = split_union(model, tiles, pairs)
     table = {}
     for name, k in kernels.items():
         row = {"avg_ms": round(k["avg_ms"], 4), "launches": k["launches"]}
@@ -573,7 +588,7 @@ def main():
         for name, W_, fl, rho in (("prefill_head_norm", Wp, hils.HILS_FLAG_HEAD_NORM_SELECT, None),
                                   ("prefill_mha_G1", Wp.with_(Hkv=Wp.Hq), 0, None),
                                   ("prefill_union_packing", Wp, U, None),
-                                  ("prefill_locality_chunk_major", Wp, 0, 0.97),
+                                  ("prefill_locality", Wp, 0, 0.97),
                                   ("prefill_locality_union_packing", Wp, U, 0.97)):
             pv, _, msv, kv = bench_prefill(torch, hils, synth, W_, args.steps, args.warmup, flags=fl, rho=rho)
             res["extra"][name] = {"ms_per_step": round(msv, 4), "tokens_per_s": round(pv.B * pv.N / (msv * 1e-3), 1),

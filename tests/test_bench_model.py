@@ -54,6 +54,18 @@ def test_union_share_counts_tiles_and_pairs():
     assert bench.union_share(idx, 4, 65) == (1.0, 1.0)
 
 
+def test_union_split_keeps_the_work():
+    m = bench.prefill_kernel_model(1, 32, 8, 8192, 8192, 128, 64, 16, 512)
+    tiles, pairs = 0.25, 0.125
+    s = bench.split_union(m, tiles, pairs)
+    assert (bench.union_limit(4, 16), bench.union_limit(8, 16)) == (40, 64)
+    names = ("k_pf_chunks", "k_pf_local", "k_pf_union")
+    assert sum(s[n]["flop"] for n in names) == m["k_pf_chunks"]["flop"] + m["k_pf_local"]["flop"]
+    assert s["k_pf_local"]["bytes"] + s["k_pf_union"]["bytes"] == m["k_pf_local"]["bytes"]
+    assert s["k_pf_chunks"]["design_bytes"] == s["k_pf_local"]["design_bytes"] == 0.875 * m["k_pf_chunks"]["design_bytes"]
+    assert bench.split_union(m, 0.0, 0.0)["k_pf_chunks"] == m["k_pf_chunks"]
+
+
 def test_decode_bytes_match_the_step():
     # one new token at position ctx of each of 32 sequences: the candidates'
     # landmarks once, the K selected chunks and the window's K/V, q in and out + lse
