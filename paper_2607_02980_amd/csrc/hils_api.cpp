@@ -134,7 +134,7 @@ int hip_status(hipError_t e, const char* what) {
 
 hils::FwdArgs fwd_args(const hils_params* p, const void* q, const void* k, const void* v, const void* lmk,
                        const float* bias, const void* q_route, const int32_t* seqlens, void* out, float* lse,
-                       int32_t* idx, void* ws, size_t ws_bytes, int decode) {
+                       int32_t* idx, void* ws, size_t ws_bytes) {
     hils::FwdArgs a;
     a.q = q; a.k = k; a.v = v; a.lmk = lmk; a.bias = bias; a.q_route = q_route; a.seqlens = seqlens;
     a.block_table = nullptr; a.num_pages = 0;
@@ -142,7 +142,6 @@ hils::FwdArgs fwd_args(const hils_params* p, const void* q, const void* k, const
     a.B = p->B; a.Hq = p->Hq; a.Hkv = p->Hkv; a.Hl = p->Hl; a.N = p->N; a.L = p->L; a.d = p->d;
     a.K = p->topk; a.W = p->window; a.scale = p->scale;
     a.bf16 = p->dtype == HILS_BF16;
-    a.decode = decode;
     a.given_idx = (p->flags & HILS_FLAG_GIVEN_IDX) ? 1 : 0;
     a.head_norm = (p->flags & HILS_FLAG_HEAD_NORM_SELECT) ? 1 : 0;
     a.union_pack = (p->flags & HILS_FLAG_UNION_PACKING) ? 1 : 0;
@@ -236,7 +235,7 @@ int hils_prefill_fwd(const hils_params* p, const void* q, const void* k, const v
     rc = check_ws(p, HILS_OP_PREFILL, workspace, ws_bytes);
     if (rc) return rc;
     const hils::FwdArgs a = fwd_args(p, q, k, v, lmk, lmk_bias, q_route, nullptr, out, lse, idx, workspace,
-                                     ws_bytes, 0);
+                                     ws_bytes);
     return hip_status(hils::launch_prefill_fwd(a, (hipStream_t)stream), "hils_prefill_fwd launch");
 }
 
@@ -249,7 +248,7 @@ int hils_decode_fwd(const hils_params* p, const void* q, const void* k_cache, co
     rc = check_ws(p, HILS_OP_DECODE, workspace, ws_bytes);
     if (rc) return rc;
     const hils::FwdArgs a = fwd_args(p, q, k_cache, v_cache, lmk_cache, lmk_bias, q_route, seqlens, out, lse, idx,
-                                     workspace, ws_bytes, 1);
+                                     workspace, ws_bytes);
     return hip_status(hils::launch_decode_fwd(a, (hipStream_t)stream), "hils_decode_fwd launch");
 }
 
@@ -270,7 +269,7 @@ int hils_decode_fwd_noalloc(const hils_params* p, const void* q, const void* k_c
     rc = hip_status(hils::decode_noalloc_scratch(&ws), "hils_decode_fwd_noalloc: device address of the array");
     if (rc) return rc;
     const hils::FwdArgs a = fwd_args(p, q, k_cache, v_cache, lmk_cache, lmk_bias, q_route, seqlens, out, lse, idx,
-                                     ws, cap, 1);
+                                     ws, cap);
     return hip_status(hils::launch_decode_fwd(a, (hipStream_t)stream), "hils_decode_fwd_noalloc launch");
 }
 
@@ -286,7 +285,7 @@ int hils_decode_paged_fwd(const hils_params* p, const void* q, const void* k_pag
     rc = check_ws(p, HILS_OP_DECODE, workspace, ws_bytes);
     if (rc) return rc;
     hils::FwdArgs a = fwd_args(p, q, k_pages, v_pages, lmk_pages, bias_pages, q_route, seqlens, out, lse, idx,
-                               workspace, ws_bytes, 1);
+                               workspace, ws_bytes);
     a.block_table = block_table;
     a.num_pages = num_pages;
     return hip_status(hils::launch_decode_fwd(a, (hipStream_t)stream), "hils_decode_paged_fwd launch");

@@ -101,6 +101,39 @@ def test_prefill_matches_oracle(name):
     run_case(name)
 
 
+@pytest.mark.parametrize("name", ["bf16_ragged_multi_tile", "bf16_window1", "bf16_bias_boosted", "bf16_route_Hl_eq_Hkv",
+                                  "bf16_G2_route_bias", "bf16_mha_G1", "bf16_G8_d128", "bf16_K32", "bf16_K64_d64",
+                                  "bf16_paper_shape_d64_G8_K32", "bf16_head_gap_150", "bf16_head_gap_150_G8_d64"])
+def test_prefill_chunk_major(name):
+    """The chunk-major records against the oracle, whatever way the sizes take by themselves: a
+    gap before a given selection keeps its tile from the union."""
+    from paper_2607_02980_amd import hils
+
+    kw, wid, bias, route, shift = CASES[name]
+    p = hils.Params(**kw)
+    host = host_inputs(p, wid, bias=bias, route=route, bias_shift=shift,
+                       head_gap=GAP_CASES[name][2] if name in GAP_CASES else None)
+    dev = to_device(host, p)
+    args = (np32(host[n]) for n in ("q", "k", "v", "lmk"))
+    extra = dict(bias=np32(host.get("bias")), q_route=np32(host.get("q_route")))
+    p.topk = min(p.topk, 63)
+    args = (oshape(p), *args)
+    idx = oracle.fwd(*args, **extra)["idx"]
+    ref = oracle.fwd(*args, idx=idx, **extra)
+    gap = torch.from_numpy(np.concatenate([np.full_like(idx[..., :1], -1), idx], -1)).cuda().contiguous()
+    p.topk += 1
+    p.flags = hils.HILS_FLAG_GIVEN_IDX
+    res = {}
+
+    def call():
+        res["r"] = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev.get("bias"), dev.get("q_route"),
+                                         idx=gap)
+
+    assert "k_pf_chunks" in kernels_of(call)
+    check_close("out", np32(res["r"][0]), ref["out"], "bf16")
+    check_lse(np32(res["r"][1]), ref["lse"], "bf16")
+
+
 def test_prefill_union_packing_forced_index():
     # union packing also serves a given selection
     from paper_2607_02980_amd import hils
@@ -279,14 +312,26 @@ def test_tiles_choose_where_the_early_ones_fill_the_chip(B, N, Hkv, G, K, by_til
     assert "k_pf_chunks" in ran and ("k_pf_union" in ran) == by_tile, ran
 
 
-@pytest.mark.parametrize("N,Hkv,G,K,d", [(6200, 2, 4, 16, 128), (5700, 1, 8, 17, 128), (6000, 1, 4, 20, 128),
-                                         (4100, 2, 1, 16, 64),
-                                         # more tiles than two per CU, where the two kinds mix
-                                         (5700, 3, 4, 16, 128), (6000, 2, 8, 17, 128)])
-def test_tiles_of_both_kinds(N, Hkv, G, K, d):
+def union_sizes(idx, G):
+    """Chunks in the union of every tile of 128 / G rows of a selection [B, Hkv, N, K]."""
+    QT = 128 // G
+    pad = -idx.shape[2] % QT
+    idx = np.pad(idx, ((0, 0), (0, 0), (0, pad), (0, 0)), constant_values=-1)
+    blk = np.sort(idx.reshape(-1, QT * idx.shape[-1]), axis=-1)
+    return ((np.diff(blk, axis=-1, prepend=-1) != 0)).sum(-1)
+
+
+@pytest.mark.parametrize("N,Hkv,G,K,d,ran", [(6200, 2, 4, 16, 128, "chunks"), (5700, 1, 8, 17, 128, "chunks"),
+                                             (6000, 1, 4, 20, 128, "chunks"), (4100, 2, 1, 16, 64, "chunks"),
+                                             (5700, 3, 4, 16, 128, "chunks"),
+                                             # enough KV groups and more tiles than two per CU: by tile
+                                             (10100, 2, 8, 17, 128, "both"), (6200, 8, 4, 16, 128, "both"),
+                                             (12000, 4, 4, 32, 128, "both")])
+def test_tiles_of_both_kinds(N, Hkv, G, K, d, ran):
     """Sequences whose early tiles take the union and whose later ones the chunk-major pass
-    (adjacent queries alike in the second half, so that some later ones take it too): every
-    row against the oracle, and bitwise the same when given the selection."""
+    (adjacent queries alike in the second half, so that some later ones take it too), and ones
+    just as long that are all chunk-major: rows of all kinds against the oracle, and bitwise
+    the same when given the selection."""
     from paper_2607_02980_amd import hils
 
     p = hils.Params(B=1, Hq=Hkv * G, Hkv=Hkv, N=N, L=-(-N // 64) * 64, d=d, topk=K, window=200)
@@ -294,12 +339,28 @@ def test_tiles_of_both_kinds(N, Hkv, G, K, d):
     alike = synth.ar1_host(host["q"].shape, 373, "bf16", 0.999)
     host["q"][:, :, N // 2:] = alike[:, :, N // 2:]
     dev = to_device(host, p)
-    out, lse, idx = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"])
+    res = {}
+
+    def call():
+        res["r"] = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"])
+
+    names = kernels_of(call)
+    assert ("k_pf_chunks" in names, "k_pf_union" in names) == (True, ran == "both"), names
+    out, lse, idx = res["r"]
+    if ran == "both":
+        small = union_sizes(idx.cpu().numpy(), G) <= (4 * K if G == 8 else 5 * K // 2)
+        half = len(small) // Hkv // 2
+        late = small.reshape(Hkv, -1)[:, half:]
+        log(f"[tiles] {small.mean():.3f} of the tiles take the union, {late.mean():.3f} of the later half")
+        assert small.any() and not small.all() and late.any()
     p.flags = hils.HILS_FLAG_GIVEN_IDX
     same, slse, _ = hils.hils_prefill_fwd(p, dev["q"], dev["k"], dev["v"], dev["lmk"], dev["bias"], idx=idx.clone())
     assert torch.equal(out, same) and torch.equal(lse, slse)
     p.flags = 0
-    args = (oshape(p), *(np32(host[n]) for n in ("q", "k", "v", "lmk")))
-    ref = oracle.fwd(*args, bias=np32(host["bias"]), idx=idx.cpu().numpy())
-    check_close("out", np32(out), ref["out"], "bf16")
-    check_lse(np32(lse), ref["lse"], "bf16")
+    # every row of the smaller cases, every 7th and the edges of tiles of the others
+    n = np.arange(N) if N * p.Hq <= 100000 else np.unique(np.r_[0:N:7, 31:N:320, 32:N:320, N - 1])
+    args = (oshape(p), *(np32(host[x]) for x in ("q", "k", "v", "lmk")))
+    ref = oracle.fwd(*args, bias=np32(host["bias"]), idx=idx.cpu().numpy(),
+                     rows=np.stack([np.zeros_like(n), n], -1).astype(np.int32))
+    check_close("out", np32(out)[:, :, n], ref["out"][:, :, n], "bf16")
+    check_lse(np32(lse)[:, :, n], ref["lse"][:, :, n], "bf16")
