@@ -100,7 +100,10 @@ typedef enum {
  * all of its rows (rows that did not select a chunk get weight 0).  Without the flag the
  * library takes this way where the tiles' unions are small (short sequences, early
  * tiles, queries that retrieve alike) and the chunk-major pass elsewhere, so the flag is
- * rarely faster.  Same results up to the rounding of the chunk-major records.  Needs no
+ * rarely faster.  Same results up to the rounding of the chunk-major records, so that a
+ * row's bits can depend on what else is in the call (batch, heads, length) through the way
+ * its tile takes; the same call gives the same bits, and a given selection the bits of the
+ * same one made in the call.  Needs no
  * workspace (hils_workspace_size reports 0 under this flag).  Ignored by the
  * fp32 path, decode and the backward. */
 #define HILS_FLAG_UNION_PACKING 8u

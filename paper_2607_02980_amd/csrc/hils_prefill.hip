@@ -993,8 +993,9 @@ __global__ __launch_bounds__(LocalCfg<G>::NT, 4) void k_pf_local(FwdArgs a, cons
         const int* myidx = s_idx + trow * a.K;
         int ptr = 0;
         // As the window's blocks: chunk u is computed from LDS buffer u % 2 while chunk u + 1
-        // is fetched into registers, one barrier per chunk.  At 128 VGPRs two workgroups
-        // share a CU and cover each other's barriers and chains (four chunks in flight in
+        // is fetched into registers, one barrier per chunk.  At 128 VGPRs (d = 128 spills 3 or 4
+        // of them, 11 to 17 with routing queries) two workgroups, where the lists leave room for
+        // both, share a CU and cover each other's barriers and chains (four chunks in flight in
         // registers, at one workgroup per CU: 139 us for 2 x 3001 tokens, 16 heads in groups
         // of 2, d = 64).  The chunk's G landmark rows and biases travel with its K/V
         // (threads < G * D / 8).
@@ -1283,7 +1284,8 @@ struct PfRun {
         // tiles chunk-major and by tile: 8000 tokens in groups of 4, i.i.d. 749 and 701 us, AR(1)
         // queries (rho 0.97) 741 and 678; groups of 8: 848 and 767, 16000 with rho 0.97: 1756 and
         // 1128; 32K, groups of 4: 3325 and 3177; K = 32, 8000: 1199 and 798.  Left out, because
-        // the second launch and the count cost more than the early tiles save there: K = 8
+        // the second launch and the count cost more than the early tiles save there (at about
+        // 8000 tokens; longer ones and queries that retrieve alike were not measured): K = 8
         // (469 and 490), K = 4 (323 and 346), groups of 2 (405 and 412) and 1 (470 and 484), d =
         // 64 (246 and 286).  (A given selection takes the same way as one made here, tile by
         // tile, except that the union does not look past gaps in a row: such tiles stay
