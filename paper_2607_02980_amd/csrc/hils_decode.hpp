@@ -772,10 +772,12 @@ __device__ __forceinline__ void scan_shared(const FwdArgs& a, const DecLayout& l
 // the landmark rows are read once for all of them; wave q selects for query q.
 // Each query row keeps its own candidate count (its own position).
 // counters: the arrival counters that the passes after the scan use and the scan clears.
+// Four waves per SIMD at NQ = 1: left to itself the compiler took 129 registers for d = 64 in
+// groups of 4, three waves (42 sequences of 125K, shared landmarks: the step 59.0 us, now 54.4).
 constexpr int kScanSelect = 0, kScanNormKeep = 1;
 constexpr int kNoCounters = 0, kPartCounters = 1, kMqCounters = 2;
 template <typename T, int D, int G, int NQ, bool PAGED>
-__global__ __launch_bounds__(kBlock) void k_dec_scan(FwdArgs a, DecLayout ly, int mode, int counters) {
+__global__ __launch_bounds__(kBlock, NQ == 1 ? 4 : 1) void k_dec_scan(FwdArgs a, DecLayout ly, int mode, int counters) {
     static_assert(NQ <= kBlock / kWave, "one selecting wave per query");
     const int ngrp = (a.N + NQ - 1) / NQ;
     const int b = blockIdx.z / ngrp, n0 = (blockIdx.z % ngrp) * NQ, g = blockIdx.y;
