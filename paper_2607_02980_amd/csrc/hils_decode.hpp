@@ -2017,7 +2017,7 @@ struct DecRun {
     static hipError_t run(const FwdArgs& a, hipStream_t s) {
         const int R = a.B * a.N;  // rows (sequence, new query); the host keeps R <= 65535
         const int cus = device_cus();
-        const DecLayout ly = dec_layout(a.B, a.N, a.Hkv, G, D, a.L, a.K, a.W, a.head_norm);
+        const DecLayout ly = dec_layout(a.B, a.N, a.Hkv, G, D, a.L, a.K, a.W, a.head_norm, a.Hl != a.Hq);
         if constexpr (sizeof(T) == 2) {
             // short caches, one new query per sequence, a workgroup per row in one round of
             // the CUs: scan, selection, parts and fusion in one launch

@@ -26,8 +26,8 @@ inline int local_pieces_max(int W) { return (W + 62) / 64 + 1; }
 // (k_dec_mq: per workgroup mq_umax union chunks x 16 tile rows); under the per-head
 // normalised ranking (HN) also, per (row, slice), the union of the G heads' top-K
 // chunks of the slice by raw score: its size, ids and G raw scores each.
-inline DecLayout dec_layout(int B, int N, int Hkv, int G, int d, int L, int K, int W,
-                                                int HN) {
+inline DecLayout dec_layout(int B, int N, int Hkv, int G, int d, int L, int K, int W, int HN,
+                            bool shared = false) {
     const int R = B * N;
     DecLayout o;
     o.nC = L / kChunk;
@@ -45,10 +45,14 @@ inline DecLayout dec_layout(int B, int N, int Hkv, int G, int d, int L, int K, i
     // scan (a wave keeps at most 16 KB of landmarks in flight, and a ragged batch leaves
     // many slices empty), the row's survivors stay within one selection of a wave (4 per
     // lane) and the workspace within the fixed array of the call without one.  Scan of 8
-    // sequences of 64K, 4 new tokens: 28.6 us with 256 workgroups of 256 chunks.
+    // sequences of 64K, 4 new tokens: 28.6 us with 256 workgroups of 256 chunks.  With one
+    // landmark head per KV group a slice's read is a quarter or less and its selection is
+    // not, so one workgroup per CU is enough (steps with 1024 and 256, shared landmarks: 16
+    // sequences of 100K, d = 64, 39.1 and 35.2 us; 24 of 60K, d = 128, 46.9 and 43.4; 8 of
+    // 100K 31.1 and 30.7).
     o.slice = kSlice;
-    const long sgroups = (long)B * ((N + 3) / 4) * Hkv;
-    while (!HN && o.slice > 64 && sgroups * ((o.nC + o.slice - 1) / o.slice) < 1024 &&
+    const long sgroups = (long)B * ((N + 3) / 4) * Hkv, full = shared && N == 1 ? 256 : 1024;
+    while (!HN && o.slice > 64 && sgroups * ((o.nC + o.slice - 1) / o.slice) < full &&
            (o.nC + o.slice / 2 - 1) / (o.slice / 2) * K <= 4 * kWave &&
            cand(o.slice / 2) + parts + mq <= HILS_DECODE_NOALLOC_SCRATCH_BYTES)
         o.slice /= 2;

@@ -81,3 +81,26 @@ def test_finer_slices_stay_within_the_fixed_array():
         coarse = al(rows * ns * K * 8) + al(rows * (K + nloc) * 4 * 132 * 4) + al(rows * ns * 4 * 8)
         size = hils.hils_workspace_size(p, hils.HILS_OP_DECODE)
         assert size <= max(coarse, hils.HILS_DECODE_NOALLOC_SCRATCH_BYTES), (B, L, K, size, coarse)
+
+
+@pytest.mark.parametrize("B,Hkv,ctx,d", [(1, 2, 4095, 64), (16, 8, 20000, 64), (3, 8, 20000, 128), (36, 8, 17000, 64)])
+def test_shared_landmarks_match_repeated_ones(B, Hkv, ctx, d):
+    """One landmark head per KV group against the same landmarks given for every query head, at
+    slices of 64 to 256 chunks (the shared scan takes longer ones): the same selection and, to
+    the rounding of the scores' sums, the same outputs."""
+    from paper_2607_02980_amd import hils
+
+    G, L = 4, -(-(ctx + 1) // 64) * 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    t = lambda *s: torch.randn(s, device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v, lmk = t(B, Hkv * G, 1, d), t(B, Hkv, L, d), t(B, Hkv, L, d), t(B, Hkv, L // 64, d)
+    res = []
+    for Hl, lm in ((Hkv, lmk), (Hkv * G, lmk.repeat_interleave(G, 1).contiguous())):
+        p = hils.Params(B=B, Hq=Hkv * G, Hkv=Hkv, Hl=Hl, N=1, L=L, d=d, topk=8, window=128)
+        ws = torch.full((hils.hils_workspace_size(p, hils.HILS_OP_DECODE),), 255, dtype=torch.uint8, device="cuda")
+        res.append(hils.hils_decode_fwd(p, q, k, v, lm, workspace=ws))
+    (o1, l1, i1), (o2, l2, i2) = res
+    same = (i1 == i2).all(-1)  # (a tie in the last bits of two scores may go either way)
+    assert same.float().mean() > 0.99
+    rows = same.repeat_interleave(G, 1)
+    assert (o1.float() - o2.float())[rows].abs().max() <= 2e-2 and (l1 - l2)[rows].abs().max() <= 2e-4
